@@ -13,19 +13,10 @@
 // that straddle span ends, the ragged tail and unaligned columns copy element
 // by element.
 //
-// Piece path (n <= kPieceMaxN): consecutive trajectories form blocks of
+// Range path (n <= kPieceMaxN): consecutive trajectories form blocks of
 // kPieceBlock; per block the rank kernel (or compact_partials_kernel) has
-// written the kept count, kept tokens and the number of pieces of at most
-// kPieceLen tokens the kept spans cut into. The copy kernel then runs one
-// 256-thread workgroup per block, writing that block's packed offsets, kept
-// ids and rejected ids, and piece workgroups (at most one resident round;
-// each takes pieces q, q + stride, ...): the workgroup scans the block
-// partials (at most 512) to find a piece's block, the 16 trajectories of the
-// block to find its span, and copies the piece with 16-byte vectors, four
-// loads in flight per thread (source loads dword-aligned, stores aligned and
-// non-temporal). Pieces are short enough that long trajectories spread over
-// many workgroups, long enough that the per-workgroup set-up is small next to
-// the copy.
+// written the kept count and kept tokens. The packed output is cut into equal
+// ranges, one workgroup per range and column (compact_range_kernel below).
 //
 // Wide path (8192 < n <= kWideMaxN): blocks of kWideBlock trajectories with
 // two-level partials, and the packed output split evenly over one resident
@@ -34,6 +25,8 @@
 // Scan path (larger pools): one workgroup scans the flags into the packed
 // offsets, kept ids, span sources and a map from each output chunk of
 // kCopyChunk elements to its first span; a second kernel copies.
+#include <algorithm>
+
 #include "device_util.hpp"
 #include "kernels.hpp"
 
@@ -197,11 +190,14 @@ __device__ __forceinline__ void copy_range_col(const CompactCols &cols, int col,
 }
 
 // ---------------------------------------------------------------------------
-// Piece path
+// Range path
 // ---------------------------------------------------------------------------
-constexpr int kPT = 256;                  // threads of a piece workgroup
+constexpr int kPT = 256;                  // threads of a copying workgroup
 constexpr int kPW = kPT / kWave;          // its waves
-constexpr int kCopyU = 4;                 // 16-byte loads in flight per thread in a piece copy
+constexpr int kCopyU = 4;                 // 16-byte loads in flight per thread in a range copy
+constexpr int64_t kRangeMin = 1024;       // tokens of a range when the batch does not fill the chip
+constexpr int64_t kRangeLen = 3584;       // tokens of a range when it does
+constexpr int64_t kWaveCopy = 2048;       // a span part of at most this many bytes is one wave's
 
 // Span length of trajectory i if kept (offsets clamped to [0, NT]), else 0.
 // (The flag and both offsets are loaded together: one round trip.)
@@ -233,191 +229,200 @@ __global__ __launch_bounds__(kWave) void compact_partials_kernel(const int64_t *
     }
     const uint32_t c = (uint32_t)__popcll(ballot(kept));
     const int64_t l = wave_sum_i64(len);
-    const int64_t pc = wave_sum_i64((len + kPieceLen - 1) / kPieceLen);
     if (lane == 0) {
         parts.cnt[blockIdx.x] = (int32_t)c;
         parts.len[blockIdx.x] = l;
-        parts.pcs[blockIdx.x] = (int32_t)pc;
     }
 }
 
-// The workgroup copies elements [d, d + m) of one column from [s, s + m).
-template <int E>
-__device__ __forceinline__ void copy_piece(const char *__restrict__ in, char *__restrict__ out, bool vec,
-                                           int64_t d, int64_t s, int64_t m) {
-    using T = typename Elem<E>::T;
-    const T *src = reinterpret_cast<const T *>(in);
-    T *dst = reinterpret_cast<T *>(out);
-    const int t = threadIdx.x;
-    const int64_t delta = s - d;
-    if (E >= 4 && vec) {
-        constexpr int VE = 16 / E;
-        const int64_t e = d + m;
-        const int64_t a0 = (d + VE - 1) / VE * VE, a1 = e / VE * VE;
-        if (a0 < a1) {
-            if (t < a0 - d) dst[d + t] = src[d + t + delta];
-            if (t < e - a1) dst[a1 + t] = src[a1 + t + delta];
-            // kCopyU loads in flight per thread, then their stores.
-            const int64_t v1 = a1 / VE;
-            int64_t v = a0 / VE + t;
-            for (; v + (kCopyU - 1) * kPT < v1; v += kCopyU * kPT) {
-                uint4 x[kCopyU];
+// kThreads threads (t = 0 .. kThreads - 1, whole waves) copy nb bytes from src
+// to dst, any alignment of either: aligned 16-byte non-temporal stores, their
+// sources as 16-byte loads at whatever byte they start on, kCopyU in flight
+// per thread; the fewer than 16 bytes before the first and after the last
+// aligned store go out as one unaligned 16-byte store each, which repeats
+// bytes of its neighbour. (One- and two-byte columns and columns off 16-byte
+// alignment went element by element before: 1024 trajectories, five columns
+// of 1 to 8 bytes at odd starts, 138 us, now 26.) The two end stores follow
+// the stream: ahead of it, the first wave waits a round trip for them (0.4 us
+// of the 50M-token step).
+template <int kThreads>
+__device__ __forceinline__ void copy_bytes(const char *__restrict__ src, char *__restrict__ dst, int64_t nb, int t) {
+    if (nb < 16) {
+        if (t < nb) dst[t] = src[t];
+        return;
+    }
+    const int64_t h = (int64_t)(-(uintptr_t)dst & 15);
+    const int64_t nv = (nb - h) / 16;
+    const char *sv = src + h;
+    uint4 *dv = reinterpret_cast<uint4 *>(dst + h);
+    int64_t v = t;
+    for (; v + (kCopyU - 1) * kThreads < nv; v += kCopyU * kThreads) {
+        uint4 x[kCopyU];
 #pragma unroll
-                for (int u = 0; u < kCopyU; ++u) x[u] = load_a4(src + (v + u * kPT) * VE + delta);
+        for (int u = 0; u < kCopyU; ++u) x[u] = load_a1(sv + (v + u * kThreads) * 16);
 #pragma unroll
-                for (int u = 0; u < kCopyU; ++u) store_nt(reinterpret_cast<uint4 *>(dst + (v + u * kPT) * VE), x[u]);
-            }
-            for (; v < v1; v += kPT) store_nt(reinterpret_cast<uint4 *>(dst + v * VE), load_a4(src + v * VE + delta));
-            return;
+        for (int u = 0; u < kCopyU; ++u) store_nt(dv + v + u * kThreads, x[u]);
+    }
+    for (; v < nv; v += kThreads) store_nt(dv + v, load_a1(sv + v * 16));
+    if (t == kThreads - 64 && h != 0) store_a1(dst, load_a1(src));
+    if (t == kThreads - 63 && h + nv * 16 != nb) store_a1(dst + nb - 16, load_a1(src + nb - 16));
+}
+
+// The block partials of at most kWave * kPL blocks, kPL consecutive ones per
+// lane, and their exclusive prefix at the lane's first.
+template <typename T, int kPL>
+struct LaneParts {
+    T v[kPL];
+    T before, total;
+    __device__ __forceinline__ void load(const T *__restrict__ x, int64_t nb) {
+        const int64_t b0 = (int64_t)lane_id() * kPL;
+        T sum = 0;
+#pragma unroll
+        for (int k = 0; k < kPL; ++k) {
+            v[k] = b0 + k < nb ? x[b0 + k] : (T)0;
+            sum += v[k];
         }
+        const int64_t incl = wave_incl_scan_i64((int64_t)sum);
+        before = (T)(incl - (int64_t)sum);
+        total = (T)readlane_i64(incl, kWave - 1);
     }
-    for (int64_t p = d + t; p < d + m; p += kPT) dst[p] = src[p + delta];
-}
+    // Prefix before block b (wave-uniform b).
+    __device__ __forceinline__ int64_t prefix(int64_t b) const {
+        int64_t p = (int64_t)before;
+#pragma unroll
+        for (int k = 0; k < kPL; ++k) p += k < (int)(b % kPL) ? (int64_t)v[k] : 0;
+        return readlane_i64(p, (int)(b / kPL));
+    }
+};
 
-// kBlk trajectories per block (at most a wave); thread t holds the partials
-// of blocks [t*kPP, (t+1)*kPP). offsets_out, kept_ids and n_kept_tokens may
-// be null (rejected ids only).
-template <int kBlk, int kPP>
-__global__ __launch_bounds__(kPT) void compact_piece_kernel(
+// Workgroups [0, n_idx) write the index outputs (packed offsets, kept ids,
+// rejected ids), one block per wave. Then workgroup n_idx + r of grid row col
+// copies packed tokens [r S, (r + 1) S) of column col, S = ceil(total / n_rng):
+// bound by memory, so the output is cut evenly whatever the spans' lengths,
+// finely enough that workgroups ending early leave room for others, and by
+// column (the ranges of one column before the next's). Every wave looks its
+// range up by itself (the block partials in its lanes, a wave scan, then the
+// block's 16 spans): no barrier and no LDS, 56 VGPRs, so that eight
+// workgroups share a CU and one's look-up hides under the others' copies. All
+// waves copy a long span part together; parts of at most kWaveCopy bytes go to
+// the waves in turn. offsets_out, kept_ids and n_kept_tokens may be null
+// (rejected ids only).
+// Against whole spans cut into pieces of 16,384 tokens with all columns in one
+// workgroup: 10M kept tokens in 3 columns 61 -> 45 us, 16.9M in 4 columns
+// 100 -> 80 us, 16.7M in one column 26 -> 25 us.
+template <int kPL>
+__global__ __launch_bounds__(kPT) void compact_range_kernel(
     const int64_t *__restrict__ off, int64_t n, int64_t NT, const uint8_t *__restrict__ keep,
-    PieceParts parts, int64_t nb, CompactCols cols, int n_cols, int64_t *__restrict__ offsets_out,
-    int32_t *__restrict__ kept_ids, int64_t *__restrict__ n_kept_tokens, int32_t *__restrict__ reject_ids,
-    int64_t budget) {
-    constexpr int kPartsPerThread = kPP;
-    static_assert(kBlk <= kWave, "a block is handled by one wave");
-    __shared__ uint32_t w_cnt[kPW], w_pcs[kPW];
-    __shared__ int64_t w_len[kPW];
-    __shared__ int64_t sel[3];
-    __shared__ int64_t piece[3];
-    const int t = threadIdx.x;
+    PieceParts parts, int64_t nb, int64_t n_idx, int64_t n_rng, CompactCols cols, int n_cols,
+    int64_t *__restrict__ offsets_out, int32_t *__restrict__ kept_ids, int64_t *__restrict__ n_kept_tokens,
+    int32_t *__restrict__ reject_ids, int64_t budget) {
+    const int lane = lane_id();
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const int64_t q = blockIdx.x;
-    if (t == 0) {
-        sel[0] = sel[1] = sel[2] = 0;
-        piece[0] = piece[1] = piece[2] = 0;   // an unmatched piece copies nothing
-    }
-
-    // 1. Exclusive prefix of the block partials; thread t holds blocks
-    //    [t * kPartsPerThread, (t + 1) * kPartsPerThread).
-    uint32_t c[kPartsPerThread], pc[kPartsPerThread];
-    int64_t l[kPartsPerThread];
-    uint32_t cs = 0, ps = 0;
-    int64_t ls = 0;
-#pragma unroll
-    for (int k = 0; k < kPartsPerThread; ++k) {
-        const int64_t b = (int64_t)t * kPartsPerThread + k;
-        c[k] = b < nb ? (uint32_t)parts.cnt[b] : 0u;
-        l[k] = b < nb ? parts.len[b] : 0;
-        pc[k] = b < nb ? (uint32_t)parts.pcs[b] : 0u;
-        cs += c[k];
-        ls += l[k];
-        ps += pc[k];
-    }
-    uint32_t tot_c, tot_p;
-    int64_t tot_l;
-    uint32_t cb = block_excl_sum_u32<kPW>(cs, tot_c, w_cnt);
-    int64_t lb = block_excl_sum_i64<kPW>(ls, tot_l, w_len);
-    uint32_t pb = block_excl_sum_u32<kPW>(ps, tot_p, w_pcs);
-    if (q == 0 && t == 0 && offsets_out) {
-        offsets_out[tot_c] = tot_l;
-        *n_kept_tokens = tot_l;
-    }
-
-    if (q < nb) {
-        // 2a. Index outputs of block q.
-#pragma unroll
-        for (int k = 0; k < kPartsPerThread; ++k) {
-            if ((int64_t)t * kPartsPerThread + k == q) {
-                sel[0] = cb;
-                sel[1] = lb;
-            }
-            cb += c[k];
-            lb += l[k];
+    LaneParts<int64_t, kPL> L;
+    if (q < n_idx) {
+        if (blockIdx.y != 0) return;
+        const int64_t b = q * kPW + wv;
+        if (b >= nb && q != 0) return;
+        const int64_t i = b * kPieceBlock + lane;
+        const bool in = lane < kPieceBlock && i < n;
+        int64_t len = 0, lo;
+        bool kept = false;
+        if (in) {
+            const int64_t k = kept_span(off, keep, i, NT, lo);
+            kept = k >= 0;
+            len = kept ? k : 0;
         }
-        __syncthreads();
-        if (t < kWave) {
-            const int64_t i = q * kBlk + t;
-            const bool in = t < kBlk && i < n;
-            int64_t len = 0, lo;
-            bool kept = false;
-            if (in) {
-                const int64_t k = kept_span(off, keep, i, NT, lo);
-                kept = k >= 0;
-                len = kept ? k : 0;
+        LaneParts<int32_t, kPL> C;
+        L.load(parts.len, nb);
+        C.load(parts.cnt, nb);
+        if (q == 0 && threadIdx.x == 0 && offsets_out) {
+            offsets_out[C.total] = L.total;
+            *n_kept_tokens = L.total;
+        }
+        if (b >= nb) return;
+        const int64_t rank = C.prefix(b) + (int64_t)__popcll(ballot(kept) & lanes_below());
+        const int64_t dst = L.prefix(b) + (wave_incl_scan_i64(len) - len);
+        if (kept) {
+            if (offsets_out) {
+                offsets_out[rank] = dst;
+                kept_ids[rank] = (int32_t)i;
             }
-            const int64_t rank = sel[0] + (int64_t)__popcll(ballot(kept) & lanes_below());
-            const int64_t dst = sel[1] + (wave_incl_scan_i64(len) - len);
-            if (kept) {
-                if (offsets_out) {
-                    offsets_out[rank] = dst;
-                    kept_ids[rank] = (int32_t)i;
-                }
-            } else if (in && reject_ids) {
-                const int64_t rr = i - rank;       // trajectories before i that were rejected
-                if (rr < budget) reject_ids[rr] = (int32_t)i;
-            }
+        } else if (in && reject_ids) {
+            const int64_t rr = i - rank;       // trajectories before i that were rejected
+            if (rr < budget) reject_ids[rr] = (int32_t)i;
         }
         return;
     }
 
-    // 2b. Pieces q - nb, q - nb + stride, ... (stride = piece workgroups in
-    //     the grid): for each, its block, then its trajectory in the block.
-    const int64_t stride = (int64_t)gridDim.x - nb;
-    for (int64_t pq = q - nb; pq < (int64_t)tot_p; pq += stride) {
-        __syncthreads();                       // the previous piece's reads of sel/piece are done
-        if (t == 0) {
-            sel[0] = sel[1] = sel[2] = 0;
-            piece[0] = piece[1] = piece[2] = 0;   // an unmatched piece copies nothing
-        }
-        __syncthreads();
-        uint32_t pbk = pb;
-        int64_t lbk = lb;
+    // Copy: packed tokens [x0, x1).
+    const int64_t r = q - n_idx;
+    const int col = blockIdx.y;
+    L.load(parts.len, nb);
+    const int64_t total = L.total < NT ? L.total : NT;   // malformed offsets could overflow the output
+    int64_t S = (total + n_rng - 1) / n_rng;
+    S = (S + 63) / 64 * 64;
+    const int64_t x0 = r * S;
+    if (x0 >= total) return;
+    const int64_t x1 = x0 + S < total ? x0 + S : total;
+
+    const int64_t E = cols.elem[col];
+    const char *in = (const char *)cols.in[col];
+    char *out = (char *)cols.out[col];
+
+    // The block holding x0: the last with tokens whose prefix is at or before it.
+    int64_t b, lb;
+    {
+        int64_t p = L.before, mb = -1, mp = 0;
 #pragma unroll
-        for (int k = 0; k < kPartsPerThread; ++k) {
-            const int64_t b = (int64_t)t * kPartsPerThread + k;
-            if (b < nb && pc[k] > 0 && (int64_t)pbk <= pq && pq < (int64_t)pbk + pc[k]) {
-                sel[0] = b;
-                sel[1] = pbk;
-                sel[2] = lbk;
+        for (int k = 0; k < kPL; ++k) {
+            if (L.v[k] > 0 && p <= x0) {
+                mb = (int64_t)lane * kPL + k;
+                mp = p;
             }
-            pbk += pc[k];
-            lbk += l[k];
+            p += L.v[k];
         }
-        __syncthreads();
-        if (t < kWave) {
-            const int64_t b = sel[0];
-            const int64_t i = b * kBlk + t;
-            int64_t len = 0, lo = 0;
-            if (t < kBlk && i < n) {
-                const int64_t k = kept_span(off, keep, i, NT, lo);
-                len = k > 0 ? k : 0;
-            }
-            const int64_t np = (len + kPieceLen - 1) / kPieceLen;
-            const int64_t np_incl = wave_incl_scan_i64(np);
-            const int64_t len_incl = wave_incl_scan_i64(len);
-            const int64_t qq = pq - sel[1];
-            if (np > 0 && np_incl - np <= qq && qq < np_incl) {
-                const int64_t k = qq - (np_incl - np);
-                piece[0] = sel[2] + (len_incl - len) + k * kPieceLen;
-                piece[1] = lo + k * kPieceLen;
-                piece[2] = (len - k * kPieceLen) < kPieceLen ? len - k * kPieceLen : kPieceLen;
-            }
+        const uint64_t m = ballot(mb >= 0);
+        const int top = m ? 63 - __clzll((long long)m) : 0;
+        b = readlane_i64(mb, top);
+        lb = readlane_i64(mp, top);
+        if (m == 0) return;
+    }
+    int turn = 0;
+    while (true) {
+        const int64_t i = b * kPieceBlock + lane;
+        int64_t len = 0, lo = 0;
+        if (lane < kPieceBlock && i < n) {
+            const int64_t k = kept_span(off, keep, i, NT, lo);
+            len = k > 0 ? k : 0;
         }
-        __syncthreads();
-        const int64_t d = piece[0], s = piece[1];
-        int64_t m = piece[2];
-        if (d >= NT || m <= 0) continue;        // overlapping (malformed) offsets overflow the output
-        if (d + m > NT) m = NT - d;
-        for (int col = 0; col < n_cols; ++col) {
-            const char *in = (const char *)cols.in[col];
-            char *out = (char *)cols.out[col];
-            const bool vec = cols.vec[col] != 0;
-            switch (cols.elem[col]) {
-                case 1: copy_piece<1>(in, out, vec, d, s, m); break;
-                case 2: copy_piece<2>(in, out, vec, d, s, m); break;
-                case 4: copy_piece<4>(in, out, vec, d, s, m); break;
-                default: copy_piece<8>(in, out, vec, d, s, m); break;
-            }
+        const int64_t incl = wave_incl_scan_i64(len);
+        const int64_t d = lb + incl - len;
+        uint64_t m = ballot(len > 0 && d < x1 && d + len > x0);
+        while (m) {
+            const int j = __ffsll((long long)m) - 1;
+            m &= m - 1;
+            const int64_t dj = readlane_i64(d, j), lj = readlane_i64(len, j), sj = readlane_i64(lo, j);
+            const int64_t a = dj > x0 ? dj : x0;
+            const int64_t e = dj + lj < x1 ? dj + lj : x1;
+            const int64_t nbytes = (e - a) * E;
+            const char *sp = in + (sj + (a - dj)) * E;
+            char *dp = out + a * E;
+            if (nbytes > kWaveCopy) copy_bytes<kPT>(sp, dp, nbytes, (int)threadIdx.x);
+            else if ((turn++ & (kPW - 1)) == wv) copy_bytes<kWave>(sp, dp, nbytes, lane);
         }
+        lb += readlane_i64(incl, kWave - 1);
+        if (lb >= x1) return;
+        // The next block with kept tokens.
+        int64_t nx = INT64_MAX;
+#pragma unroll
+        for (int k = kPL - 1; k >= 0; --k) {
+            const int64_t c = (int64_t)lane * kPL + k;
+            if (L.v[k] > 0 && c > b) nx = c;
+        }
+        const uint64_t mm = ballot(nx != INT64_MAX);
+        if (!mm) return;
+        b = readlane_i64(nx, __ffsll((long long)mm) - 1);
     }
 }
 
@@ -440,8 +445,8 @@ constexpr int kSpanT = kPT;               // spans in one copy table: four block
 constexpr int kSpanU = 8;                 // 16-byte loads in flight per thread in a span copy
 struct SpanTable {
     int32_t start[kSpanT + 1];   // first slot of each span; [kSpanT] = slots in the table
-    int64_t dst[kSpanT];         // destination of each span's first slot (bytes or elements)
-    int64_t src[kSpanT];         // its source
+    int64_t dst[kSpanT];         // byte offset of each span's first slot
+    int64_t src[kSpanT];         // byte offset of its source
 };
 
 // The span holding slot g: the last span whose first slot is <= g.
@@ -452,41 +457,30 @@ __device__ __forceinline__ int span_find(const SpanTable &tb, int32_t g) {
     return j;
 }
 
-// Thread t brings span t's range [a, b) and shift del (source - destination)
-// in elements; the slots are groups of `per` elements at multiples of `per`
-// inside the range, [v0, v1) the part they cover (v0 = v1 when none), so that
-// [a, v0) and [v1, b) each hold fewer than `per` elements.
-__device__ __forceinline__ void span_table(SpanTable &tb, uint32_t *wsum, int64_t a, int64_t b, int64_t del,
-                                           int per, int64_t &v0, int64_t &v1) {
-    v0 = (a + per - 1) / per * per;
-    v1 = b / per * per;
-    if (v1 < v0) v1 = v0;
-    if (v0 > b) v0 = v1 = b;
-    const uint32_t cnt = (uint32_t)((v1 - v0) / per);
-    uint32_t tot;
-    const uint32_t ex = block_excl_sum_u32<kPW>(cnt, tot, wsum);
+// Thread t brings span t's destination range [a, b) in elements and its shift
+// del (source - destination). The slots are the aligned 16-byte vectors of
+// the destination, their sources 16-byte loads at whatever byte they start
+// on; each thread then copies the fewer than 16 bytes at each end of its own
+// range as one unaligned vector that repeats bytes of its neighbour (byte by
+// byte in a range shorter than a vector), all loads first.
+__device__ __forceinline__ void copy_spans_col(const CompactCols &cols, int col, int64_t a, int64_t b, int64_t del,
+                                               SpanTable &tb, uint32_t *wsum) {
+    const int64_t E = cols.elem[col];
+    // Offsets from the last 16-byte boundary at or before the column's start.
+    const int64_t ph = (int64_t)((uintptr_t)cols.out[col] & 15);
+    const char *src = (const char *)cols.in[col] - ph;
+    char *dst = (char *)cols.out[col] - ph;
     const int t = threadIdx.x;
+    const int64_t a0 = a * E + ph, b0 = b * E + ph, dl = del * E;
+    int64_t v0 = (a0 + 15) / 16 * 16, v1 = b0 / 16 * 16;
+    if (v1 < v0) v0 = v1 = b0;
+    __syncthreads();                           // the previous table is no longer read
+    uint32_t tot;
+    const uint32_t ex = block_excl_sum_u32<kPW>((uint32_t)((v1 - v0) / 16), tot, wsum);
     tb.start[t] = (int32_t)ex;
     if (t == kPT - 1) tb.start[kSpanT] = (int32_t)tot;
     tb.dst[t] = v0;
-    tb.src[t] = v0 + del;
-}
-
-// Columns of 4- or 8-byte elements with 16-byte aligned pointers: the slots
-// are the aligned 16-byte destination vectors (sources at least 4-byte
-// aligned, one dwordx4 load each); each thread then copies the elements at
-// its own range's ends (fewer than 16 bytes at each end, all loads first).
-template <int E>
-__device__ void copy_spans_vec(const char *__restrict__ in, char *__restrict__ out, int64_t a, int64_t b,
-                               int64_t del, SpanTable &tb, uint32_t *wsum) {
-    using T = typename Elem<E>::T;
-    constexpr int VE = 16 / E;
-    const T *src = reinterpret_cast<const T *>(in);
-    T *dst = reinterpret_cast<T *>(out);
-    const int t = threadIdx.x;
-    __syncthreads();                           // the previous table is no longer read
-    int64_t v0, v1;
-    span_table(tb, wsum, a, b, del, VE, v0, v1);
+    tb.src[t] = v0 + dl;
     __syncthreads();
     const int32_t total = tb.start[kSpanT];
     for (int32_t g0 = t; g0 < total; g0 += kSpanU * kPT) {
@@ -496,7 +490,7 @@ __device__ void copy_spans_vec(const char *__restrict__ in, char *__restrict__ o
             const int32_t g = g0 + u * kPT;
             if (g < total) {
                 const int j = span_find(tb, g);
-                x[u] = load_a4(src + tb.src[j] + (int64_t)(g - tb.start[j]) * VE);
+                x[u] = load_a1(src + tb.src[j] + (int64_t)(g - tb.start[j]) * 16);
             }
         }
 #pragma unroll
@@ -504,60 +498,18 @@ __device__ void copy_spans_vec(const char *__restrict__ in, char *__restrict__ o
             const int32_t g = g0 + u * kPT;
             if (g < total) {
                 const int j = span_find(tb, g);
-                store_nt(reinterpret_cast<uint4 *>(dst + tb.dst[j] + (int64_t)(g - tb.start[j]) * VE), x[u]);
+                store_nt(reinterpret_cast<uint4 *>(dst + tb.dst[j] + (int64_t)(g - tb.start[j]) * 16), x[u]);
             }
         }
     }
-    T h[VE - 1], e[VE - 1];
-#pragma unroll
-    for (int k = 0; k < VE - 1; ++k) {
-        if (a + k < v0) h[k] = src[a + k + del];
-        if (v1 + k < b) e[k] = src[v1 + k + del];
-    }
-#pragma unroll
-    for (int k = 0; k < VE - 1; ++k) {
-        if (a + k < v0) dst[a + k] = h[k];
-        if (v1 + k < b) dst[v1 + k] = e[k];
-    }
-}
-
-// Any other column: one element per slot.
-template <int E>
-__device__ void copy_spans_elem(const char *__restrict__ in, char *__restrict__ out, int64_t a, int64_t b,
-                                int64_t del, SpanTable &tb, uint32_t *wsum) {
-    using T = typename Elem<E>::T;
-    const T *src = reinterpret_cast<const T *>(in);
-    T *dst = reinterpret_cast<T *>(out);
-    const int t = threadIdx.x;
-    __syncthreads();
-    int64_t v0, v1;
-    span_table(tb, wsum, a, b, del, 1, v0, v1);
-    __syncthreads();
-    const int32_t total = tb.start[kSpanT];
-    for (int32_t g = t; g < total; g += kPT) {
-        const int j = span_find(tb, g);
-        const int64_t r = g - tb.start[j];
-        dst[tb.dst[j] + r] = src[tb.src[j] + r];
-    }
-}
-
-// Range [a, b) of a column, shift del, in elements.
-__device__ __forceinline__ void copy_spans_col(const CompactCols &cols, int col, int64_t a, int64_t b, int64_t del,
-                                               SpanTable &tb, uint32_t *wsum) {
-    const char *in = (const char *)cols.in[col];
-    char *out = (char *)cols.out[col];
-    const bool vec = cols.vec[col] != 0;
-    switch (cols.elem[col]) {
-        case 1: copy_spans_elem<1>(in, out, a, b, del, tb, wsum); break;
-        case 2: copy_spans_elem<2>(in, out, a, b, del, tb, wsum); break;
-        case 4:
-            if (vec) copy_spans_vec<4>(in, out, a, b, del, tb, wsum);
-            else copy_spans_elem<4>(in, out, a, b, del, tb, wsum);
-            break;
-        default:
-            if (vec) copy_spans_vec<8>(in, out, a, b, del, tb, wsum);
-            else copy_spans_elem<8>(in, out, a, b, del, tb, wsum);
-            break;
+    if (b0 - a0 >= 16) {
+        uint4 h, e;
+        if (a0 < v0) h = load_a1(src + a0 + dl);
+        if (v1 < b0) e = load_a1(src + b0 - 16 + dl);
+        if (a0 < v0) store_a1(dst + a0, h);
+        if (v1 < b0) store_a1(dst + b0 - 16, e);
+    } else {
+        for (int64_t p = a0; p < b0; ++p) dst[p] = src[p + dl];
     }
 }
 
@@ -858,7 +810,7 @@ CompactWs compact_ws_carve(void *ws, int64_t n, int64_t n_tokens) {
     w.chunk_first = (int32_t *)p;  p += align256((size_t)map_capacity(n_tokens) * 4);
     w.parts.cnt = (int32_t *)p;    p += align256(nb * 4);
     w.parts.len = (int64_t *)p;    p += align256(nb * 8);
-    w.parts.pcs = (int32_t *)p;    p += align256(nb * 4);
+    p += align256(nb * 4);         // spare: keeps the workspace size that callers know
     const size_t ng = (size_t)wide_groups(n);
     w.parts.gcnt = (int32_t *)p;   p += align256(ng * 4);
     w.parts.glen = (int64_t *)p;
@@ -873,11 +825,11 @@ size_t compact_ws_bytes(int64_t n, int64_t n_tokens) {
 }
 
 bool compact_piece_ok(int64_t n, int64_t n_tokens) {
-    return n <= kPieceMaxN && n_tokens / kPieceLen < ((int64_t)1 << 30);
+    return n <= kPieceMaxN && n_tokens < kPartsMaxTokens;
 }
 
 bool compact_wide_ok(int64_t n, int64_t n_tokens) {
-    return n <= kWideMaxN && n_tokens / kPieceLen < ((int64_t)1 << 30);
+    return n <= kWideMaxN && n_tokens < kPartsMaxTokens;
 }
 
 hipError_t launch_compact_partials(const int64_t *offsets, int64_t n, int64_t n_tokens,
@@ -897,28 +849,37 @@ hipError_t launch_compact_pieces(const int64_t *offsets, int64_t n, int64_t n_to
                                  int64_t *offsets_out, int32_t *kept_ids, int64_t *n_kept_tokens,
                                  int32_t *reject_ids, int64_t budget, int64_t max_kept,
                                  hipStream_t stream, int blk, bool copy) {
-    // Block workgroups, then the piece workgroups: a kept span of len tokens
-    // has at most len / kPieceLen + 1 pieces, so all kept spans together have
-    // at most max_kept + n_tokens / kPieceLen.
-    // Past one resident round of workgroups (8 per CU) the piece workgroups
-    // loop over the pieces instead.
     const int64_t nb = (n + blk - 1) / blk;
-    const int64_t kept_bound = max_kept < 0 ? 0 : (max_kept > n ? n : max_kept);
-    int64_t piece_wgs = copy ? kept_bound + n_tokens / kPieceLen + 1 : 0;
-    const int64_t round = resident_waves() / 16 * 8 - nb;
-    if (round > 0 && piece_wgs > round) piece_wgs = round;
-    if (copy && piece_wgs < 1) piece_wgs = 1;
-    const int64_t grid = (nb > 0 ? nb : 1) + piece_wgs;
-    const int64_t per = (nb + kPT - 1) / kPT;
-#define PACE_PIECES(B, P)                                                                                      \
-    return launch(kPhaseCompact, compact_piece_kernel<B, P>, dim3((unsigned)grid), dim3(kPT), stream, offsets, n, \
-                  n_tokens, keep, parts, nb, cols, copy ? n_cols : 0, offsets_out, kept_ids, n_kept_tokens,      \
-                  reject_ids, budget)
     if (blk == kPieceBlock) {
-        if (per > 2) return hipErrorInvalidValue;
-        PACE_PIECES(kPieceBlock, 2);
+        if (nb > 8 * kWave) return hipErrorInvalidValue;
+        const int64_t n_idx = nb > 0 ? (nb + kPW - 1) / kPW : 1;
+        // Ranges per column. max_kept / n of the tokens is the expected batch:
+        // as many ranges as fill the chip once (8 workgroups per CU over all
+        // columns) while they hold kRangeMin tokens, up to 12 per CU and column
+        // while they hold kRangeLen. Finer ranges even out the workgroups' end
+        // times, but each pays its look-up: at 4870 trajectories of 620 tokens
+        // and four columns, 2040 workgroups take 2 us less than 3500; at 10M
+        // kept tokens and three columns, 2436 to 3072 ranges of a column take
+        // 2 us less than 683 and 3 us less than 4096.
+        int64_t n_rng = 0;
+        if (copy && n_cols > 0) {
+            const int64_t cus = resident_waves() / 16;
+            const int64_t kept = max_kept < 0 ? 0 : std::min(max_kept, n);
+            const int64_t est = n > 0 ? (int64_t)((double)n_tokens * ((double)kept / (double)n)) : 0;
+            const int64_t fill = std::min(est / kRangeMin, cus * 8 / n_cols);
+            const int64_t fine = std::min(est / kRangeLen, cus * 12);
+            n_rng = std::max<int64_t>(std::max(fill, fine), 1);
+        }
+        const dim3 grid((unsigned)(n_idx + n_rng), (unsigned)(copy && n_cols > 0 ? n_cols : 1));
+#define PACE_RANGES(P)                                                                                          \
+    return launch(kPhaseCompact, compact_range_kernel<P>, grid, dim3(kPT), stream, offsets, n,    \
+                  n_tokens, keep, parts, nb, n_idx, n_rng, cols, copy ? n_cols : 0, offsets_out, kept_ids,        \
+                  n_kept_tokens, reject_ids, budget)
+        if (nb <= kWave) PACE_RANGES(1);
+        if (nb <= 4 * kWave) PACE_RANGES(4);
+        PACE_RANGES(8);
+#undef PACE_RANGES
     }
-#undef PACE_PIECES
     if (blk != kWideBlock || (nb + kGroupBlocks - 1) / kGroupBlocks > kWideMaxGroups) return hipErrorInvalidValue;
     // Every workgroup indexes up to four blocks and copies an even share of
     // the output: one resident round (four per CU) when copying.

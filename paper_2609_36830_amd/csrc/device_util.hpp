@@ -71,7 +71,7 @@ __device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
 __device__ __forceinline__ int64_t wave_incl_scan_i64(int64_t v) {
     return (int64_t)wave_scan_u64((uint64_t)v, 0ull, [](uint64_t a, uint64_t b) { return a + b; });
 }
-// Inclusive scans inside each row of 16 lanes (row_shr 1, 2, 4, 8): lane
+// Inclusive scan inside each row of 16 lanes (row_shr 1, 2, 4, 8): lane
 // 16 r + 15 ends with the sum of its row.
 __device__ __forceinline__ int64_t row_incl_scan_i64(int64_t v) {
     uint64_t x = (uint64_t)v;
@@ -80,13 +80,6 @@ __device__ __forceinline__ int64_t row_incl_scan_i64(int64_t v) {
     x += dpp_u64<0x114, 0xf>(0ull, x);
     x += dpp_u64<0x118, 0xf>(0ull, x);
     return (int64_t)x;
-}
-__device__ __forceinline__ uint32_t row_incl_scan_u32(uint32_t x) {
-    x += dpp_u32<0x111, 0xf>(0u, x);
-    x += dpp_u32<0x112, 0xf>(0u, x);
-    x += dpp_u32<0x114, 0xf>(0u, x);
-    x += dpp_u32<0x118, 0xf>(0u, x);
-    return x;
 }
 // Wave-wide reductions, broadcast to every lane.
 __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
@@ -183,6 +176,16 @@ typedef unsigned pace_v4u_a4 __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ uint4 load_a4(const void *p) {
     const pace_v4u_a4 x = *reinterpret_cast<const pace_v4u_a4 *>(p);
     return make_uint4(x.x, x.y, x.z, x.w);
+}
+// 16 bytes at any address (one dwordx4 access: gfx950 runs with unaligned
+// access enabled).
+typedef unsigned pace_v4u_a1 __attribute__((ext_vector_type(4), aligned(1)));
+__device__ __forceinline__ uint4 load_a1(const void *p) {
+    const pace_v4u_a1 x = *reinterpret_cast<const pace_v4u_a1 *>(p);
+    return make_uint4(x.x, x.y, x.z, x.w);
+}
+__device__ __forceinline__ void store_a1(void *p, const uint4 &v) {
+    *reinterpret_cast<pace_v4u_a1 *>(p) = pace_v4u_a1{v.x, v.y, v.z, v.w};
 }
 __device__ __forceinline__ void store_nt(uint4 *p, const uint4 &v) {
     const pace_v4u x = {v.x, v.y, v.z, v.w};

@@ -4,11 +4,11 @@
 //   1. score_reduce   (score.hip)    every tag read once, per-chunk pieces
 //   2. score_finalize (score.hip)    one thread per trajectory: the score
 //   3. rank           (select.hip)   exact rank by counting -> keep flags,
-//                                    plus per-block kept counts, kept tokens
-//                                    and piece counts
-//   4. compact_piece  (compact.hip)  one workgroup per block writes the packed
+//                                    plus per-block kept counts and tokens
+//   4. compact_range  (compact.hip)  one wave per block writes the packed
 //                                    offsets, kept ids and rejected ids; one
-//                                    per piece of a kept span copies it
+//                                    workgroup per range of the packed output
+//                                    and column copies it
 //
 // The same results as pace_score, pace_budget, pace_select and pace_compact
 // called in sequence, in four launches instead of six. Pools beyond the rank

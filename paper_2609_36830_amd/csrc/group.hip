@@ -153,13 +153,11 @@ __global__ __launch_bounds__(kAdmT) void group_admit_kernel(const int64_t *__res
         // Rows of 16 lanes are blocks of kPieceBlock trajectories.
         static_assert(kPieceBlock == 16 && kAdmT % kPieceBlock == 0, "a block is one row of 16 lanes");
         const int64_t l_row = row_incl_scan_i64(len);
-        const uint32_t p_row = row_incl_scan_u32((uint32_t)((len + kPieceLen - 1) / kPieceLen));
         const uint32_t c_row = (uint32_t)__popcll((ballot(kept) >> (lane & ~15)) & 0xffffull);
         const int64_t b = i / kPieceBlock;
         if ((lane & 15) == 15 && b * kPieceBlock < n) {
             parts.cnt[b] = (int32_t)c_row;
             parts.len[b] = l_row;
-            parts.pcs[b] = (int32_t)p_row;
         }
     }
 }

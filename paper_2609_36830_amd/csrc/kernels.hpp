@@ -103,17 +103,15 @@ constexpr int kSelectMaxItems = 16;   // keys held in registers per thread
 // Pools up to this size are selected by the multi-workgroup rank-by-counting
 // kernel; larger pools by the single-workgroup radix select.
 constexpr int64_t kRankMaxN = 8192;
-// ---- compaction by pieces: block partials ----------------------------------
-// Consecutive trajectories form blocks of kPieceBlock; a kept span of len
-// tokens is cut into ceil(len / kPieceLen) pieces. Per block: kept count,
-// kept tokens and pieces (lengths from offsets clamped to [0, n_tokens]).
+// ---- compaction by ranges: block partials -----------------------------------
+// Consecutive trajectories form blocks of kPieceBlock. Per block: kept count
+// and kept tokens (lengths from offsets clamped to [0, n_tokens]).
 constexpr int kPieceBlock = 16;
-constexpr int64_t kPieceLen = 16384;
 constexpr int64_t kPieceMaxN = 8192;   // at most 512 blocks
+constexpr int64_t kPartsMaxTokens = (int64_t)1 << 44;   // pools beyond take the scan path
 struct PieceParts {
     int32_t *cnt;
     int64_t *len;
-    int32_t *pcs;      // blocks of kPieceBlock only
     int32_t *gcnt;     // wide blocks only: per group of kGroupBlocks blocks, the sums of cnt and len
     int64_t *glen;
 };
@@ -202,13 +200,13 @@ CompactWs compact_ws_carve(void *ws, int64_t n, int64_t n_tokens);
 size_t compact_ws_bytes(int64_t n, int64_t n_tokens);
 hipError_t launch_compact_copy(const CompactCols &cols, int n_cols, int64_t n_tokens,
                                const int64_t *offsets_out, const CompactWs &w, hipStream_t stream);
-// Piece path (at most kPieceMaxN trajectories): one workgroup per block
-// writes that block's packed offsets, kept ids and rejected ids; one
-// workgroup per piece copies it. reject_ids may be NULL; when given, the ids
-// with keep == 0 go there in ascending order (at most `budget` of them).
+// Range path (at most kPieceMaxN trajectories): one wave per block writes that
+// block's packed offsets, kept ids and rejected ids; one workgroup per range of
+// the packed output and column copies it. reject_ids may be NULL; when given,
+// the ids with keep == 0 go there in ascending order (at most `budget` of them).
 // The block partials come from the rank kernel or from launch_compact_partials.
-// max_kept bounds the number of kept trajectories (n when unknown); the grid
-// holds max_kept + n_tokens / kPieceLen piece workgroups.
+// max_kept bounds the number of kept trajectories (n when unknown); it sizes
+// the grid.
 bool compact_piece_ok(int64_t n, int64_t n_tokens);
 // Blocks of kWideBlock trajectories: pools of up to kWideMaxN.
 bool compact_wide_ok(int64_t n, int64_t n_tokens);

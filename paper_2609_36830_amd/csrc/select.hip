@@ -317,11 +317,9 @@ __device__ __forceinline__ void rank_block(const double (&v)[kKeys], uint64_t kq
             const int64_t len = kept ? span : 0;
             const uint32_t c = (uint32_t)__popcll(ballot(kept));
             const int64_t l = wave_sum_i64(len);
-            const int64_t pc = wave_sum_i64((len + kPieceLen - 1) / kPieceLen);
             if (t == 0) {
                 parts.cnt[blockIdx.x] = (int32_t)c;
                 parts.len[blockIdx.x] = l;
-                parts.pcs[blockIdx.x] = (int32_t)pc;
             }
         }
     }
@@ -458,7 +456,7 @@ hipError_t launch_select(const double *score, int64_t n, int64_t budget, uint8_t
     if (n == 0) return hipSuccess;
     const int64_t items = (n + kT - 1) / kT;
     if (n <= kRankMaxN) {
-        hipError_t e = launch_rank(score, n, budget, keep, nullptr, 0, PieceParts{nullptr, nullptr, nullptr},
+        hipError_t e = launch_rank(score, n, budget, keep, nullptr, 0, PieceParts{},
                                    stream);
         if (e != hipSuccess || budget == 0) return e;
         if (items <= 1)

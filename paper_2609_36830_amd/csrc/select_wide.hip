@@ -591,7 +591,7 @@ WideWs wide_ws_carve(void *ws, int64_t n) {
     const int64_t nb = (n + kWideBlock - 1) / kWideBlock;
     w.parts.cnt = (int32_t *)p; p += align256((size_t)nb * 4);
     w.parts.len = (int64_t *)p; p += align256((size_t)nb * 8);
-    w.parts.pcs = (int32_t *)p; p += align256((size_t)nb * 4);
+    p += align256((size_t)nb * 4);  // spare: keeps the workspace size that callers know
     const int64_t ng = wide_groups(n);
     w.parts.gcnt = (int32_t *)p; p += align256((size_t)ng * 4);
     w.parts.glen = (int64_t *)p;

@@ -96,8 +96,8 @@ __device__ __forceinline__ int64_t shfl_xor_i64(int64_t v, int m) {
 }
 
 // kParts: also writes the compaction's block partials of the keep flags
-// (kept count, kept tokens, pieces per block of kPieceBlock trajectories,
-// lengths from offsets clamped to [0, NT]); a block is two adjacent threads.
+// (kept count and kept tokens per block of kPieceBlock trajectories, lengths
+// from offsets clamped to [0, NT]); a block is two adjacent threads.
 template <bool kParts>
 __global__ __launch_bounds__(kST) void stream_admit_kernel(
     const double *__restrict__ score, int64_t n, int64_t B,
@@ -172,7 +172,7 @@ __global__ __launch_bounds__(kST) void stream_admit_kernel(
         const uint32_t before = block_excl_sum_u32<kSNW>(c, tot, wsum);
         int64_t rb = run_ret + before;          // retained before item i0 + q
         uint32_t d = 0;
-        uint32_t k_cnt = 0, k_pcs = 0;
+        uint32_t k_cnt = 0;
         int64_t k_len = 0;
 #pragma unroll
         for (int q = 0; q < kSItems; ++q) {
@@ -193,20 +193,17 @@ __global__ __launch_bounds__(kST) void stream_admit_kernel(
                     const int64_t len = ob[q + 1] > ob[q] ? ob[q + 1] - ob[q] : 0;
                     k_cnt += 1;
                     k_len += len;
-                    k_pcs += (uint32_t)((len + kPieceLen - 1) / kPieceLen);
                 }
             }
         }
         if constexpr (kParts) {
             const uint32_t c2 = k_cnt + (uint32_t)__shfl_xor((int)k_cnt, 1, kWave);
-            const uint32_t p2 = k_pcs + (uint32_t)__shfl_xor((int)k_pcs, 1, kWave);
             const int64_t l2 = k_len + shfl_xor_i64(k_len, 1);
             const int64_t b0 = base + (int64_t)(t & ~1) * kSItems;     // the block's first trajectory
             if ((t & 1) == 0 && b0 < n) {
                 const int64_t blk = b0 / kPieceBlock;
                 parts.cnt[blk] = (int32_t)c2;
                 parts.len[blk] = l2;
-                parts.pcs[blk] = (int32_t)p2;
             }
         }
         uint32_t dtot;
