@@ -1,6 +1,9 @@
 // pace_validate kernels for gfx950: device check of the preconditions of
 // Lemma 1 (every generated token has v_t <= c(tau) <= j; versions are
-// non-negative) and of the CSR layout and prefix window. Not on the hot path.
+// non-negative) and of the CSR layout and prefix window. One kernel clears the
+// error word; the other's first workgroups check offsets, completion versions
+// and the window, one entry per thread, and the rest check the tags, one wave
+// per chunk of tokens.
 #include "../../include/pace.h"
 #include "device_util.hpp"
 #include "kernels.hpp"
@@ -13,11 +16,10 @@ constexpr int64_t kValChunk = 8192;   // tokens per wave
 
 __global__ void validate_init_kernel(int32_t *err) { *err = 0; }
 
-// One thread per trajectory (plus the window): offsets and completion versions.
-__global__ __launch_bounds__(256) void validate_meta_kernel(
-    const int64_t *__restrict__ off, int64_t n, int64_t NT, const int32_t *__restrict__ completion,
-    int32_t V, const double *__restrict__ window, int64_t W, int32_t *err) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Offsets and completion versions of trajectory i, and window entry i.
+__device__ __forceinline__ int32_t meta_bits(int64_t i, const int64_t *__restrict__ off, int64_t n, int64_t NT,
+                                             const int32_t *__restrict__ completion, int32_t V,
+                                             const double *__restrict__ window, int64_t W) {
     int32_t bad = 0;
     if (i == 0 && (off[0] != 0 || off[n] != NT)) bad |= PACE_BAD_OFFSETS;
     if (i < n) {
@@ -29,39 +31,93 @@ __global__ __launch_bounds__(256) void validate_meta_kernel(
         const double a = window[i];
         if (__builtin_isnan(a) || (i + 1 < W && !(a <= window[i + 1]))) bad |= PACE_BAD_WINDOW;
     }
-    if (bad) atomicOr(err, bad);
+    return bad;
 }
 
-// One wave per token chunk: every tag is -1 or within [0, c] of its trajectory.
-__global__ __launch_bounds__(256) void validate_tags_kernel(
+// Largest tag + 1, as an unsigned number, of tokens [a, e): below -1 it is
+// huge, -1 gives 0. U vectors of four tags per lane in flight; a lane past the
+// end reads the last four tags again, so no load sits behind a branch.
+template <int U>
+__device__ __forceinline__ uint32_t max_tag1(const int32_t *__restrict__ tags, int64_t a, int64_t e, uint32_t m) {
+    const int64_t last = e - 4;
+    uint4 x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int64_t p = a + ((int64_t)u * kWave + lane_id()) * 4;
+        x[u] = load_a4(tags + (p < last ? p : last));
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        m = max(max(m, max(x[u].x + 1u, x[u].y + 1u)), max(x[u].z + 1u, x[u].w + 1u));
+    return m;
+}
+
+// Workgroups [0, n_meta): 256 entries each of the offsets, completion versions
+// and window. The others: one wave per chunk of kValChunk tokens, every tag -1
+// or within [0, c] of its trajectory. The wave takes the trajectories of its
+// chunk in turn, 64 offsets and versions at a time in its lanes, and each
+// trajectory's tokens as whole vectors against one limit, so that it is bound
+// by the tags' bytes: 21.7M tags in 2048 trajectories 111 us (64 tags a round
+// trip, each window's offsets loaded again) -> 16.4 us.
+// With malformed offsets the tag bit is that of this walk: trajectories in
+// order from the one holding the chunk's first token, each from where the one
+// before it ended (but not behind the 64-token window that the walk has
+// reached) to its own end.
+__global__ __launch_bounds__(256) void validate_kernel(
     const int32_t *__restrict__ tags, const int64_t *__restrict__ off, int64_t n, int64_t NT,
-    const int32_t *__restrict__ completion, int64_t n_chunks, int32_t *err) {
+    const int32_t *__restrict__ completion, int32_t V, const double *__restrict__ window, int64_t W, int64_t n_meta,
+    int64_t n_chunks, int32_t *err) {
+    if ((int64_t)blockIdx.x < n_meta) {
+        const int32_t bits = meta_bits((int64_t)blockIdx.x * blockDim.x + threadIdx.x, off, n, NT, completion, V, window, W);
+        if (bits) atomicOr(err, bits);
+        return;
+    }
     const int lane = lane_id();
-    const int64_t chunk = (int64_t)blockIdx.x * 4 + threadIdx.x / kWave;
+    const int64_t chunk = ((int64_t)blockIdx.x - n_meta) * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     if (chunk >= n_chunks) return;
     const int64_t cs = chunk * kValChunk;
     const int64_t ce = (cs + kValChunk < NT) ? cs + kValChunk : NT;
     int64_t cur = wave_last_le(off, n, cs);
-    if (cur < 0) cur = 0;             // malformed offsets are reported by the meta kernel
-    bool bad = false;
-    while (cur < n && clamp64(off[cur + 1], 0, NT) <= cs) ++cur;
-    for (int64_t w = cs; w < ce; w += kWave) {
-        const int64_t p = w + lane;
-        const bool in = p < ce;
-        const int32_t x = in ? tags[p] : -1;
-        // trajectories that meet this window of 64 tokens
-        int64_t lo = w;
-        const int64_t we = (w + kWave < ce) ? w + kWave : ce;
-        while (cur < n) {
-            const int64_t hi = clamp64(off[cur + 1], 0, NT);
-            const int32_t c = completion[cur];
-            if (in && p >= lo && p < hi && x != -1 && (x < 0 || x > c)) bad = true;
-            if (hi >= we) break;
+    if (cur < 0) cur = 0;             // malformed offsets are reported by the meta workgroups
+    bool bad = false, started = false;
+    int64_t lo = cs, front = cs;      // the walk's position, and its 64-token window
+    for (; cur < n; cur += kWave) {
+        const int64_t i = cur + lane;
+        const int64_t h = i < n ? clamp64(off[i + 1], 0, NT) : 0;
+        const int32_t cl = i < n ? completion[i] : 0;
+        const uint32_t lim = cl < -1 ? 0u : (uint32_t)cl + 1u;
+        const int cnt = (int)(n - cur < kWave ? n - cur : kWave);
+        int k = 0;
+        if (!started) {               // skip what ends at or before the chunk's start
+            const uint64_t m = ballot(i < n && h > cs);
+            if (!m) continue;
+            k = __ffsll((long long)m) - 1;
+            started = true;
+        }
+        for (; k < cnt; ++k) {
+            const int64_t hi = readlane_i64(h, k);
+            int64_t a = lo > front ? lo : front;
+            const int64_t e = hi < ce ? hi : ce;
+            if (a < e) {
+                const uint32_t top = (uint32_t)readlane_i32((int32_t)lim, k);
+                uint32_t m = 0;
+                if (e - a < 4) {
+                    if (a + lane < e) m = (uint32_t)tags[a + lane] + 1u;
+                } else {
+                    for (; e - a > 4 * 4 * kWave; a += 8 * 4 * kWave) m = max_tag1<8>(tags, a, e, m);
+                    if (a < e) m = max_tag1<4>(tags, a, e, m);
+                }
+                bad |= m > top;
+            }
+            if (hi >= ce) {
+                cur = n;              // the chunk is done
+                break;
+            }
+            if (hi > front) front = cs + (hi - cs) / 64 * 64;
             lo = hi;
-            ++cur;
         }
     }
-    if (__popcll(ballot(bad)) && lane == 0) atomicOr(err, PACE_BAD_TAG);
+    if (ballot(bad) && lane == 0) atomicOr(err, PACE_BAD_TAG);
 }
 
 }  // namespace
@@ -73,15 +129,10 @@ hipError_t launch_validate(const int32_t *tags, const int64_t *offsets, int64_t 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int64_t m = (n + 1 > W) ? n + 1 : W;
-    validate_meta_kernel<<<(unsigned)((m + 255) / 256), 256, 0, stream>>>(offsets, n, n_tokens, completion, V, window, W, err_word);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (n > 0 && n_tokens > 0) {
-        const int64_t ch = (n_tokens + kValChunk - 1) / kValChunk;
-        validate_tags_kernel<<<(unsigned)((ch + 3) / 4), 256, 0, stream>>>(tags, offsets, n, n_tokens, completion, ch, err_word);
-        e = hipGetLastError();
-    }
-    return e;
+    const int64_t n_meta = (m + 255) / 256;
+    const int64_t ch = n > 0 ? (n_tokens + kValChunk - 1) / kValChunk : 0;
+    return launch(-1, validate_kernel, dim3((unsigned)(n_meta + (ch + 3) / 4)), dim3(256), stream, tags, offsets, n,
+                  n_tokens, completion, V, window, W, n_meta, ch, err_word);
 }
 
 }  // namespace pace

@@ -1,0 +1,121 @@
+"""pace_validate's tag check at the edges of its chunks (8192 tokens), vectors
+and trajectories: a version one above its trajectory's completion, planted at
+each edge, is found; one equal to it is not. Malformed offsets give the flags of
+the documented walk."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+from tests.test_gpu_parity import D, H
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+V = 100
+
+
+@pytest.fixture(scope="module")
+def pace():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2609_36830_amd as pace
+    return pace
+
+
+def _pool(kind, rng):
+    if kind == "mixed":
+        L = np.concatenate([[0, 1, 2, 3, 4, 5, 0, 0], rng.integers(0, 9, 150), [1023, 1025, 8190, 2, 8192, 1],
+                            np.zeros(200, np.int64), rng.integers(200, 3000, 12), [0, 0, 7]])
+    elif kind == "long":
+        L = np.array([30001, 1, 50000])
+    else:
+        L = rng.integers(0, 3, 9000)
+    off = np.concatenate([[0], np.cumsum(L)]).astype(np.int64)
+    comp = rng.integers(0, V + 1, len(L)).astype(np.int32)
+    tags = np.repeat(comp, L).astype(np.int32)           # every tag equals its completion version
+    tags[rng.random(len(tags)) < 0.2] = -1
+    return off, comp, tags
+
+
+def _run(pace, tags, off, comp, lead=0):
+    buf = torch.zeros(len(tags) + lead, dtype=torch.int32, device="cuda:0")
+    buf[lead:] = D(tags)
+    e = pace.pace_validate(buf[lead:], D(off), D(comp), V)
+    torch.cuda.synchronize()
+    return int(H(e)[0])
+
+
+@pytest.mark.parametrize("kind", ["mixed", "long", "tiny"])
+def test_bad_tag_at_every_edge(pace, kind):
+    rng = np.random.default_rng(5)
+    off, comp, tags = _pool(kind, rng)
+    N, n = len(tags), len(comp)
+    traj = np.repeat(np.arange(n), np.diff(off))
+    assert oracle.validate(tags, off, comp, V) == 0
+    at = {0, 1, 2, 3, 4, N - 1, N - 2, N - 4, N - 5}
+    at |= {p + d for p in range(8192, N, 8192) for d in (-5, -4, -1, 0, 1, 3)}
+    at |= {int(p) + d for p in rng.choice(off, 12) for d in (-1, 0, 1)}
+    at |= {p + d for p in (256, 1024, 2048, 3072) for d in (-1, 0)}
+    at = sorted(p for p in at if 0 <= p < N)
+    for lead in (0, 1, 3):
+        sys.stdout.write("[gpu] validate %s lead %d tokens %d\n" % (kind, lead, N))
+        sys.stdout.flush()
+        assert _run(pace, tags, off, comp, lead) == 0
+        for p in at:
+            for bad in (int(comp[traj[p]]) + 1, -2):
+                t = tags.copy()
+                t[p] = bad
+                assert oracle.validate(t, off, comp, V) != 0
+                assert _run(pace, t, off, comp, lead) == pace.BAD_TAG, (p, bad)
+
+
+def _walk(tags, off, comp, chunk=8192):
+    """The tag flag by the walk that the kernel documents, token by token."""
+    n, N = len(comp), len(tags)
+    for cs in range(0, N, chunk):
+        ce = min(cs + chunk, N)
+        a, base, ln = off, 0, n + 1                      # the kernel's 64-ary search for the last offset <= cs
+        cur = None
+        while ln > 64:
+            step = (ln + 63) // 64
+            cnt = sum(1 for k in range(64) if base + k * step < base + ln and a[base + k * step] <= cs)
+            if cnt == 0:
+                cur = base - 1
+                break
+            nb = base + (cnt - 1) * step
+            ln = min(base + ln - nb, step)
+            base = nb
+        if cur is None:
+            cur = base + sum(1 for k in range(ln) if a[base + k] <= cs) - 1
+        cur = max(cur, 0)
+        clip = lambda x: min(max(int(x), 0), N)
+        while cur < n and clip(off[cur + 1]) <= cs:
+            cur += 1
+        for w in range(cs, ce, 64):
+            lo, we = w, min(w + 64, ce)
+            while cur < n:
+                hi = clip(off[cur + 1])
+                x = tags[lo if lo > w else w:min(hi, we)]
+                if ((x != -1) & ((x < 0) | (x > comp[cur]))).any():
+                    return True
+                if hi >= we:
+                    break
+                lo = hi
+                cur += 1
+    return False
+
+
+def test_malformed_offsets_give_the_walks_flags(pace):
+    rng = np.random.default_rng(11)
+    for k in range(24):
+        off, comp, tags = _pool("mixed" if k % 2 else "tiny", rng)
+        bad = off.copy()
+        j = rng.integers(0, len(off), 1 + k % 5)
+        bad[j] = rng.integers(-5, len(tags) + 5, len(j))
+        want = pace.BAD_TAG if _walk(tags, bad, comp) else 0
+        mono = (np.diff(bad) >= 0).all() and bad[0] == 0 and bad[-1] == len(tags)
+        want |= 0 if mono else pace.BAD_OFFSETS
+        sys.stdout.write("[gpu] validate malformed %d want %d\n" % (k, want))
+        sys.stdout.flush()
+        assert _run(pace, tags, bad, comp) == want
