@@ -8,10 +8,13 @@
 //
 // Diagnostics (Sec. 4, the staleness distribution diagnostics): histograms
 // of K_wait, K_gen and K_eff over the candidates, retained versus rejected,
-// and exact integer totals per class. One workgroup per metric and one for
-// the totals, each over every trajectory: an LDS histogram with LDS atomics
-// (integer, so the result does not depend on their order) written once at the
-// end to its own rows. No zeroed global memory is needed.
+// and exact integer totals per class. Small pools: one workgroup per metric
+// and one for the totals, each over every trajectory: an LDS histogram with
+// LDS atomics (integer, so the result does not depend on their order) written
+// once at the end to its own rows; one launch, no zeroed memory. Larger pools:
+// a kernel that clears the outputs, then workgroups over slices of the pool,
+// each with all three histograms and the totals, added to the outputs with
+// integer atomics.
 #include "device_util.hpp"
 #include "kernels.hpp"
 
@@ -206,6 +209,109 @@ __global__ __launch_bounds__(kDT) void diagnostics_kernel(
     }
 }
 
+// ---- larger pools: slices of the pool ---------------------------------------
+__global__ __launch_bounds__(kDT) void diagnostics_clear_kernel(int64_t *__restrict__ hist_out, int n_hist,
+                                                               int64_t *__restrict__ totals_out) {
+    for (int x = threadIdx.x; x < n_hist; x += kDT) hist_out[x] = 0;
+    if (threadIdx.x < 8) totals_out[threadIdx.x] = 0;
+}
+
+__device__ __forceinline__ void add_i64(int64_t *p, int64_t v) {
+    if (v != 0) atomicAdd(reinterpret_cast<unsigned long long *>(p), (unsigned long long)v);
+}
+
+// One trajectory per thread and round; the three bin searches of a trajectory
+// run side by side. Latency-bound: 65,536 trajectories and 64 bins take 6.7 us
+// (and 1.4 for the clearing) over 64 workgroups, where four workgroups over
+// every trajectory took 38.7.
+__global__ __launch_bounds__(kDT) void diagnostics_slice_kernel(
+    const double *__restrict__ score, const int64_t *__restrict__ S, const int64_t *__restrict__ T,
+    const int32_t *__restrict__ completion, int32_t V, const uint8_t *__restrict__ keep, int64_t n,
+    const double *__restrict__ edges, int nbins, int64_t *__restrict__ hist_out, int64_t *__restrict__ totals_out) {
+    __shared__ double e_lds[3][kEdgeStride];
+    __shared__ uint32_t h_lds[3 * 2 * (kDiagBinsMax + 2)];
+    __shared__ int64_t wtot[kDT / kWave][8];
+    const int t = threadIdx.x;
+    const int nb1 = nbins + 1, nb2 = nbins + 2;
+    const int top = 1 << (31 - __builtin_clz((unsigned)nb1));   // largest power of two <= nb1
+    int64_t a_c = 0, a_s = 0, a_t = 0, r_c = 0, r_s = 0, r_t = 0;
+    int64_t n_a = 0, n_r = 0;   // wave-uniform
+    bool first = true;
+    for (int64_t base = (int64_t)blockIdx.x * kDT; base < n; base += (int64_t)gridDim.x * kDT) {
+        const bool in = base + t < n;
+        const int64_t i = in ? base + t : n - 1;
+        const uint8_t kp = keep[i];
+        const int32_t c = completion[i];
+        const int64_t sv = S[i], tv = T[i];
+        const double sc = score[i];
+        if (first) {              // the loads above do not wait for the edges
+            for (int M = 0; M < 3; ++M) {
+                for (int x = t; x < nb1; x += kDT) e_lds[M][x] = edges[M * nb1 + x];
+                for (int x = nb1 + t; x < 2 * top; x += kDT) e_lds[M][x] = __builtin_nan("");
+            }
+            for (int x = t; x < 6 * nb2; x += kDT) h_lds[x] = 0;
+            __syncthreads();
+            first = false;
+        }
+        const double m[3] = {(double)V - (double)c, (tv > 0) ? (double)sv / (double)tv : 0.0, sc};
+        // The search of diagnostics_metric (the largest probe is 2 * top - 2).
+        int pos[3] = {0, 0, 0};
+        for (int step = top; step > 0; step >>= 1) {
+#pragma unroll
+            for (int M = 0; M < 3; ++M) {
+                const int nxt = pos[M] + step;
+                pos[M] = (e_lds[M][nxt - 1] <= m[M]) ? nxt : pos[M];
+            }
+        }
+        const bool ret = in && kp != 0;
+        if (in) {
+#pragma unroll
+            for (int M = 0; M < 3; ++M) atomicAdd(&h_lds[(2 * M + (ret ? 1 : 0)) * nb2 + pos[M]], 1u);
+        }
+        n_a += __popcll(ballot(in));
+        n_r += __popcll(ballot(ret));
+        a_c += in ? (int64_t)c : 0;
+        a_s += in ? sv : 0;
+        a_t += in ? tv : 0;
+        r_c += ret ? (int64_t)c : 0;
+        r_s += ret ? sv : 0;
+        r_t += ret ? tv : 0;
+    }
+    const int64_t sums[6] = {wave_sum_i64(a_c), wave_sum_i64(a_s), wave_sum_i64(a_t),
+                             wave_sum_i64(r_c), wave_sum_i64(r_s), wave_sum_i64(r_t)};
+    if (lane_id() == 0) {
+#pragma unroll
+        for (int q = 0; q < 6; ++q) wtot[t / kWave][q] = sums[q];
+        wtot[t / kWave][6] = n_a;
+        wtot[t / kWave][7] = n_r;
+    }
+    __syncthreads();
+    for (int x = t; x < 6 * nb2; x += kDT) add_i64(&hist_out[x], (int64_t)h_lds[x]);
+    // Lane q < 8 of the last wave: total q (the rejected class is the
+    // difference of all and retained, sum (V - c) = V * count - sum c).
+    if (t >= kDT - kWave && lane_id() < 8) {
+        const int q = lane_id();
+        int64_t A[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        for (int w = 0; w < kDT / kWave; ++w)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) A[k] += wtot[w][k];
+        const bool r = q >= 4;
+        const int64_t cnt = r ? A[7] : A[6] - A[7];
+        const int64_t s0 = r ? A[3] : A[0] - A[3], s1 = r ? A[4] : A[1] - A[4], s2 = r ? A[5] : A[2] - A[5];
+        const int k = q & 3;
+        add_i64(&totals_out[q], k == 0 ? cnt : k == 1 ? (int64_t)V * cnt - s0 : k == 2 ? s1 : s2);
+    }
+}
+
+// The one-launch form grows with the pool and with the search, the slices cost
+// a second launch. Calls back to back, one launch against slices: 64 bins, 8192
+// trajectories 7.2 / 9.7 us, 12,288 8.7 / 9.7, 16,384 11.0 / 9.7, 65,536 38.3 /
+// 9.7; 1000 bins, 4096 trajectories 7.7 / 10.3, 6000 10.7 / 10.4, 8192 12.5 /
+// 10.5.
+constexpr int64_t kDiagOneLaunchMax = 12288;
+inline bool diag_one_launch(int64_t n, int nbins) { return n * (nbins > 256 ? 2 : 1) <= kDiagOneLaunchMax; }
+constexpr int64_t kDiagSlicesMax = 128;
+
 }  // namespace
 
 hipError_t launch_stale_k(const int64_t *S, const int64_t *T, const int32_t *completion, int32_t V, int64_t n,
@@ -218,6 +324,13 @@ hipError_t launch_stale_k(const int64_t *S, const int64_t *T, const int32_t *com
 hipError_t launch_diagnostics(const double *score, const int64_t *S, const int64_t *T, const int32_t *completion,
                               int32_t V, const uint8_t *keep, int64_t n, const double *edges, int nbins,
                               int64_t *hist, int64_t *totals, hipStream_t stream) {
+    if (!diag_one_launch(n, nbins)) {
+        const int64_t g = (n + kDT - 1) / kDT;
+        hipError_t e = launch(-1, diagnostics_clear_kernel, dim3(1), dim3(kDT), stream, hist, 6 * (nbins + 2), totals);
+        if (e != hipSuccess) return e;
+        return launch(kPhaseAux, diagnostics_slice_kernel, dim3((unsigned)(g < kDiagSlicesMax ? g : kDiagSlicesMax)),
+                      dim3(kDT), stream, score, S, T, completion, V, keep, n, edges, nbins, hist, totals);
+    }
     return launch(kPhaseAux, diagnostics_kernel, dim3(4), dim3(kDT), stream, score, S, T, completion, V, keep, n, edges,
                   nbins, hist, totals);
 }
