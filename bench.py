@@ -68,7 +68,7 @@ def parse():
 # trajectories (rank path), and larger ones (level-0 histogram of the cut
 # search, cut-and-classify, merge-path compaction over blocks of 64
 # trajectories)
-PHASES = ((0, "score_reduce"), (1, "score_finalize"), (2, "rank"), (3, "compact_piece"))
+PHASES = ((0, "score_traj"), (2, "rank"), (3, "compact_piece"))
 PHASES_WIDE = ((0, "score_reduce"), (1, "score_finalize"), (2, "cut_hist"), (6, "classify"),
                (3, "compact_wide"))
 
@@ -95,6 +95,9 @@ def reduce_chunks(n_tokens, cus):
 
 def kernel_bytes(pool, n_keep_tok, col_bytes, W, use_prefix, cus):
     """Algorithmic bytes of each kernel of the fused step:
+    score_traj     4 B per tag, 8 B per offset, completion 4 B, prefix score 8 B
+                   and the window when used read; score 8 B, S and T 16 B and
+                   the rank's copy of the score 8 B written;
     score_reduce   4 B per tag read, 8 B per offset, 16 B per trajectory
                    (piece sum and count written), 16 B per chunk (carry);
     score_finalize offsets (2 x 8 B), completion 4 B, prefix score 8 B and
@@ -127,6 +130,7 @@ def kernel_bytes(pool, n_keep_tok, col_bytes, W, use_prefix, cus):
     kept = n - min(budget, n)
     pre = (8 * n + 8 * W) if use_prefix else 0
     return {
+        "score_traj": 4 * N + 8 * (n + 1) + 4 * n + pre + 32 * n,
         "score_reduce": 4 * N + 8 * (n + 1) + 16 * n + 16 * chunks,
         "score_finalize": 16 * n + 4 * n + pre + 16 * n + 16 * chunks + 8 * n + 16 * n + (16 * groups if wide else 0),
         "rank": 8 * n + 16 * n + n + 16 * blocks,

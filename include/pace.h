@@ -189,12 +189,13 @@ int pace_validate(const int32_t *tags, const int64_t *offsets, int64_t n_traj, i
  * pace_budget on the host, then pace_score, pace_select and pace_compact on
  * the device, with the same arguments and results as those four calls made
  * in sequence (every output is bit-identical to theirs). The device work is
- * four dependent launches instead of six: the rank kernel also writes the
- * per-block partials the compaction needs, and the compaction writes the
- * rejected ids. Pools of 8192 < n_traj <= 262144 select across the whole
- * device (a level-0 histogram, then a kernel that finds the cut and writes
- * the keep flags and partials: five launches); larger pools run the separate
- * calls' kernels.
+ * three dependent launches instead of five or six: the score kernel; the rank
+ * kernel, which also finishes trajectories too long for one workgroup and
+ * writes the per-block partials the compaction needs; and the compaction,
+ * which writes the rejected ids. Pools of 8192 < n_traj <= 262144 select
+ * across the whole device (a level-0 histogram, then a kernel that finds the
+ * cut and writes the keep flags and partials: five launches); larger pools run
+ * the separate calls' kernels.
  *
  * occupancy, capacity, r_hat_inout, budget_out: as pace_budget ([host]).
  * score_out, gen_sum_out, gen_count_out: as pace_score (gen_* may be NULL).
@@ -405,9 +406,11 @@ int pace_diagnostics(const double *score, const int64_t *gen_sum, const int64_t 
  * table of at most PACE_PHASE_COUNT event pairs, empty except between
  * pace_time_next_kernel and the return of the next device call on that
  * thread. Calls on other threads never see it.
- * phase: PACE_PHASE_REDUCE (token reduction of pace_score), PACE_PHASE_FINALIZE
- *   (score finalisation), PACE_PHASE_SELECT (the rank kernel, the
- *   single-workgroup select of the largest pools, the streaming draw, or in
+ * phase: PACE_PHASE_REDUCE (token reduction of pace_score; the score kernel
+ *   where scores are formed by trajectory), PACE_PHASE_FINALIZE (score
+ *   finalisation, or the kernel that finishes long trajectories; in pools of up
+ *   to 8192 trajectories the fused steps have neither), PACE_PHASE_SELECT (the
+ *   rank kernel, the single-workgroup select of the largest pools, the streaming draw, or in
  *   pace_group_filter_step the rank over groups),
  *   PACE_PHASE_COMPACT (the compaction copy kernel), PACE_PHASE_PREFIX (the
  *   Prefix Forgetting Score kernel), PACE_PHASE_AUX (the single kernel of

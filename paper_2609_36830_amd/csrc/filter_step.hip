@@ -1,24 +1,26 @@
 // pace_filter_step: the whole filter step (Algorithm 1, trainer side) on
 // one stream, every phase spread over the whole device:
 //
-//   1. score_reduce   (score.hip)    every tag read once, per-chunk pieces
-//   2. score_finalize (score.hip)    one thread per trajectory: the score
-//   3. rank           (select.hip)   exact rank by counting -> keep flags,
-//                                    plus per-block kept counts and tokens
-//   4. compact_range  (compact.hip)  one wave per block writes the packed
+//   1. score_traj     (score_traj.hip) every tag read once, one workgroup per
+//                                    trajectory: S, T and the score
+//   2. rank           (select.hip)   exact rank by counting -> keep flags,
+//                                    plus per-block kept counts and tokens;
+//                                    joins trajectories summed in pieces
+//   3. compact_range  (compact.hip)  one wave per block writes the packed
 //                                    offsets, kept ids and rejected ids; one
 //                                    workgroup per range of the packed output
 //                                    and column copies it
 //
 // The same results as pace_score, pace_budget, pace_select and pace_compact
-// called in sequence, in four launches instead of six. Pools beyond the rank
-// kernel's limit (8192 trajectories) take the selection spread over the chip
-// instead of the rank (select_wide.hip: the finalize also writes per-group
-// key extremes and clears the level-0 histogram, then cut_hist, and classify,
-// where every workgroup finds the cut and writes keep flags, the partials of
-// blocks of 64 trajectories and their group sums) and compact_wide (an even
-// merge-path split of the packed output); pools beyond that path's limit use
-// the separate calls' kernels.
+// called in sequence, in three launches. Pools beyond the rank kernel's limit
+// (8192 trajectories) take the selection spread over the chip instead of the
+// rank (select_wide.hip): the scores by trajectory or, for short ones, by
+// chunks (score.hip: score_reduce, score_finalize), with per-group key extremes
+// and the level-0 histogram cleared by the second of their kernels; then
+// cut_hist, and classify, where every workgroup finds the cut and writes keep
+// flags, the partials of blocks of 64 trajectories and their group sums; and
+// compact_wide (an even merge-path split of the packed output). Pools beyond
+// that path's limit use the separate calls' kernels.
 #include "device_util.hpp"
 #include "kernels.hpp"
 
@@ -47,13 +49,24 @@ hipError_t launch_filter_step(const int32_t *tags, const int64_t *offsets, int64
     const bool rank_path = n <= kRankMaxN && compact_piece_ok(n, n_tokens);
     const bool wide_path = !rank_path && compact_wide_ok(n, n_tokens);
     const WideWs ww = wide_ws_carve(sel_ws, n);
-    int64_t chunk_len = 0;
-    hipError_t e = launch_score_reduce(tags, offsets, n, n_tokens, V, sws, vec_ok, stream, &chunk_len);
-    if (e != hipSuccess) return e;
-    e = launch_score_finalize(offsets, n, n_tokens, completion, V, prefix, window, W, use_prefix,
-                              w_wait, gamma, chunk_len, score, gen_sum, gen_count, sws, stream,
-                              wide_path ? ww.mmin : nullptr, wide_path ? ww.mmax : nullptr,
-                              wide_path ? ww.hist : nullptr);
+    const ScoreArgs sa{offsets, n, n_tokens, completion, V, use_prefix ? 1 : 0, gamma, prefix, window, W, w_wait,
+                       score, gen_sum, gen_count};
+    ScoreJoin join{};
+    hipError_t e;
+    if (rank_path) {
+        e = launch_score_unjoined(tags, sa, sws, vec_ok, stream, &join);
+    } else if (wide_path && score_by_traj(n, n_tokens)) {
+        e = launch_score_traj(tags, sa, sws, stream);
+        if (e == hipSuccess) e = launch_score_join(sa, sws, stream, ww.mmin, ww.mmax, ww.hist);
+    } else if (wide_path) {
+        int64_t chunk_len = 0;
+        e = launch_score_reduce(tags, offsets, n, n_tokens, V, sws, vec_ok, stream, &chunk_len);
+        if (e == hipSuccess)
+            e = launch_score_finalize(offsets, n, n_tokens, completion, V, prefix, window, W, use_prefix, w_wait, gamma,
+                                      chunk_len, score, gen_sum, gen_count, sws, stream, ww.mmin, ww.mmax, ww.hist);
+    } else {
+        e = launch_score(tags, sa, sws, vec_ok, stream);
+    }
     if (e != hipSuccess) return e;
     if (wide_path) {
         const CompactWs cw = compact_ws_carve(cws_base, n, n_tokens);
@@ -68,7 +81,7 @@ hipError_t launch_filter_step(const int32_t *tags, const int64_t *offsets, int64
     }
     if (rank_path) {
         const CompactWs cw = compact_ws_carve(cws_base, n, n_tokens);
-        e = launch_rank(score, n, budget, keep, offsets, n_tokens, cw.parts, stream);
+        e = launch_rank(score, n, budget, keep, offsets, n_tokens, cw.parts, stream, join);
         if (e != hipSuccess) return e;
         // The rank rejects exactly min(budget, n) trajectories.
         const int64_t n_kept = n - (budget < n ? budget : n);

@@ -19,12 +19,13 @@ namespace {
 // One thread per group: the members' scores added in member order, then one
 // division by the member count (the oracle's order, so the result is
 // bit-identical). An empty group scores 0.
+template <bool kJoin>
 __global__ __launch_bounds__(256) void group_score_kernel(const double *__restrict__ score, int64_t n,
                                                          const int64_t *__restrict__ go, int64_t ng,
-                                                         double *__restrict__ out) {
+                                                         double *__restrict__ out, ScoreJoin join) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= ng) return;
-    out[g] = group_mean(score, n, go, g);
+    out[g] = group_mean<kJoin>(score, n, go, g, join);
 }
 
 // One wave per group: every member takes its group's keep flag.
@@ -58,7 +59,8 @@ __global__ __launch_bounds__(kAdmT) void group_admit_kernel(const int64_t *__res
                                                            const uint8_t *__restrict__ gkeep,
                                                            const int64_t *__restrict__ off, int64_t NT,
                                                            uint8_t *__restrict__ keep, PieceParts parts,
-                                                           int32_t *__restrict__ reject_gids, int64_t budget) {
+                                                           int32_t *__restrict__ reject_gids, int64_t budget,
+                                                           ScoreJoin join) {
     __shared__ int64_t s_go[kAdmStage + 1];
     __shared__ int64_t s_gs;
     __shared__ uint32_t wsum[kAdmT / kWave];
@@ -66,6 +68,13 @@ __global__ __launch_bounds__(kAdmT) void group_admit_kernel(const int64_t *__res
     const int t = threadIdx.x, lane = lane_id();
     const int64_t a = (int64_t)blockIdx.x * kAdmT;
     const int64_t i = a + t;
+
+    // Scores, S and T of the trajectories that were summed in pieces (the
+    // group means joined them on their own).
+    if (join.cap && i < n) {
+        const double m = join.ws.traj[i];
+        if (is_join_mark(m)) write_joined(i, m, join);
+    }
 
     // Loads that need no search: the trajectory's span, the rejected-group
     // flags before this workgroup's groups (strided) and its own group flag.
@@ -177,10 +186,14 @@ __global__ __launch_bounds__(256) void group_validate_kernel(const int64_t *__re
 }  // namespace
 
 hipError_t launch_group_score(const double *score, int64_t n, const int64_t *group_offsets, int64_t ng,
-                              double *group_score, hipStream_t stream) {
+                              double *group_score, hipStream_t stream, const ScoreJoin &join) {
     if (ng == 0) return hipSuccess;
-    return launch(kPhaseAux, group_score_kernel, dim3((unsigned)((ng + 255) / 256)), dim3(256), stream, score, n,
-                  group_offsets, ng, group_score);
+    const dim3 grid((unsigned)((ng + 255) / 256));
+    if (join.cap)
+        return launch(kPhaseAux, group_score_kernel<true>, grid, dim3(256), stream, (const double *)join.ws.traj, n,
+                      group_offsets, ng, group_score, join);
+    return launch(kPhaseAux, group_score_kernel<false>, grid, dim3(256), stream, score, n, group_offsets, ng,
+                  group_score, join);
 }
 
 hipError_t launch_group_expand(const int64_t *group_offsets, int64_t ng, int64_t n, const uint8_t *group_keep,
@@ -192,15 +205,16 @@ hipError_t launch_group_expand(const int64_t *group_offsets, int64_t ng, int64_t
 
 hipError_t launch_group_admit(const int64_t *group_offsets, int64_t ng, int64_t n, const uint8_t *group_keep,
                               const int64_t *offsets, int64_t n_tokens, uint8_t *keep, const PieceParts &parts,
-                              int32_t *reject_group_ids, int64_t budget, bool wide, hipStream_t stream) {
+                              int32_t *reject_group_ids, int64_t budget, bool wide, hipStream_t stream,
+                              const ScoreJoin &join) {
     const int64_t items = n > ng ? n : ng;
     const int64_t wgs = items > 0 ? (items + kAdmT - 1) / kAdmT : 0;
     if (wgs == 0) return hipSuccess;
     if (wide)
         return launch(kPhaseAux, group_admit_kernel<true>, dim3((unsigned)wgs), dim3(kAdmT), stream, group_offsets,
-                      ng, n, group_keep, offsets, n_tokens, keep, parts, reject_group_ids, budget);
+                      ng, n, group_keep, offsets, n_tokens, keep, parts, reject_group_ids, budget, join);
     return launch(kPhaseAux, group_admit_kernel<false>, dim3((unsigned)wgs), dim3(kAdmT), stream, group_offsets, ng,
-                  n, group_keep, offsets, n_tokens, keep, parts, reject_group_ids, budget);
+                  n, group_keep, offsets, n_tokens, keep, parts, reject_group_ids, budget, join);
 }
 
 hipError_t launch_group_validate(const int64_t *group_offsets, int64_t ng, int64_t n, int32_t *err,
@@ -229,27 +243,31 @@ hipError_t launch_group_filter_step(const int32_t *tags, const int64_t *offsets,
     void *cws = p;
     p += align256(compact_ws_bytes(N, n_tokens));
     void *sel_ws = p;
-    hipError_t e = launch_score(tags, offsets, n, n_tokens, completion, V, prefix, window, W, use_prefix,
-                                w_wait, gamma, score, gen_sum, gen_count, sws, vec_ok, stream);
-    if (e != hipSuccess) return e;
     const bool pieces = compact_piece_ok(n, n_tokens);
-    if (ng <= kRankMaxN && (pieces || compact_wide_ok(n, n_tokens))) {
+    const bool fused = ng <= kRankMaxN && (pieces || compact_wide_ok(n, n_tokens));
+    const ScoreArgs sa{offsets, n, n_tokens, completion, V, use_prefix ? 1 : 0, gamma, prefix, window, W, w_wait,
+                       score, gen_sum, gen_count};
+    ScoreJoin join{};
+    hipError_t e = fused ? launch_score_unjoined(tags, sa, sws, vec_ok, stream, &join)
+                         : launch_score(tags, sa, sws, vec_ok, stream);
+    if (e != hipSuccess) return e;
+    if (fused) {
         // Group scores inside the rank over groups; one kernel for the
         // members' flags, the compaction's partials (blocks of 16, or of 64
         // with group sums for the merge-path compaction) and the rejected ids.
         const CompactWs cw = compact_ws_carve(cws, N, n_tokens);
         if ((ng + kRankQ - 1) / kRankQ * n <= kGroupRankLoads) {
-            e = launch_group_rank(score, n, group_offsets, ng, budget, group_score, group_keep, stream);
+            e = launch_group_rank(score, n, group_offsets, ng, budget, group_score, group_keep, stream, join);
         } else {
             // Every rank workgroup re-forming every mean would read the
             // scores ng / kRankQ times over: form them once.
-            e = launch_group_score(score, n, group_offsets, ng, group_score, stream);
+            e = launch_group_score(score, n, group_offsets, ng, group_score, stream, join);
             if (e == hipSuccess)
                 e = launch_rank(group_score, ng, budget, group_keep, nullptr, 0, PieceParts{}, stream);
         }
         if (e != hipSuccess) return e;
         e = launch_group_admit(group_offsets, ng, n, group_keep, offsets, n_tokens, keep, cw.parts,
-                               reject_group_ids, budget, !pieces, stream);
+                               reject_group_ids, budget, !pieces, stream, join);
         if (e != hipSuccess) return e;
         return launch_compact_pieces(offsets, n, n_tokens, keep, cw.parts, cols, n_cols, offsets_out, kept_ids,
                                      n_kept_tokens, nullptr, 0, n, stream, pieces ? kPieceBlock : kWideBlock);

@@ -67,11 +67,35 @@ inline int64_t score_max_chunks(int64_t n_tokens) {
     return (n_tokens + kScoreChunkMin - 1) / kScoreChunkMin;
 }
 
+// Inputs and outputs of the score, as its kernels take them.
+struct ScoreArgs {
+    const int64_t *off;
+    int64_t n, NT;
+    const int32_t *completion;
+    int32_t V;
+    int use_prefix, gamma;
+    const double *prefix, *window;
+    int64_t W;
+    double w_wait;
+    double *score;
+    int64_t *gen_sum, *gen_count;   // may be null
+};
+
 struct ScoreWorkspace {
+    double *traj;         // [n]   score_traj: the scores, or a mark where pieces are to be joined (the space of part_sum)
     uint64_t *part_sum;   // [n]   sum of (tag+1) over generated tokens of the piece that starts the segment
     int64_t *part_cnt;    // [n]   generated-token count of that piece
     uint64_t *carry_sum;  // [chunks] piece of the segment that straddles the chunk start
     int64_t *carry_cnt;   // [chunks]
+};
+
+// What a kernel that reads the scores after launch_score_traj needs to finish
+// the trajectories that were summed in pieces (score_math.hpp). cap = 0: there
+// are none, the scores are complete.
+struct ScoreJoin {
+    ScoreArgs a;
+    ScoreWorkspace ws;
+    int64_t cap;
 };
 
 size_t score_ws_bytes(int64_t n, int64_t n_tokens);
@@ -91,11 +115,25 @@ hipError_t launch_score_finalize(const int64_t *offsets, int64_t n, int64_t n_to
                                  int64_t *gen_count, const ScoreWorkspace &ws, hipStream_t stream,
                                  uint64_t *mmin = nullptr, uint64_t *mmax = nullptr,
                                  uint32_t *hist0 = nullptr);
-hipError_t launch_score(const int32_t *tags, const int64_t *offsets, int64_t n, int64_t n_tokens,
-                        const int32_t *completion, int32_t V, const double *prefix,
-                        const double *window, int64_t W, bool use_prefix, double w_wait, int gamma,
-                        double *score, int64_t *gen_sum, int64_t *gen_count,
-                        const ScoreWorkspace &ws, bool vec_ok, hipStream_t stream);
+// Whether the score is formed by trajectory (score_traj.hip) rather than over
+// equal chunks of tokens, and the most tokens that one workgroup then sums.
+bool score_by_traj(int64_t n, int64_t n_tokens);
+int64_t score_traj_cap(int64_t n, int64_t n_tokens);
+// Scores, S and T of every trajectory of at most score_traj_cap tokens, and
+// ws.traj; longer ones are left for the joining kernel or reader.
+hipError_t launch_score_traj(const int32_t *tags, const ScoreArgs &a, const ScoreWorkspace &ws, hipStream_t stream);
+// launch_score_traj, or the chunked kernels; *join says what is left to the
+// kernels that read the scores.
+hipError_t launch_score_unjoined(const int32_t *tags, const ScoreArgs &a, const ScoreWorkspace &ws, bool vec_ok,
+                                 hipStream_t stream, ScoreJoin *join);
+// Scores, S and T of the trajectories of more than score_traj_cap tokens; with
+// mmin/mmax non-null the key extremes and the cleared hist0 as in
+// launch_score_finalize. Launches nothing when no trajectory can be that long
+// and no extremes are asked for.
+hipError_t launch_score_join(const ScoreArgs &a, const ScoreWorkspace &ws, hipStream_t stream,
+                             uint64_t *mmin = nullptr, uint64_t *mmax = nullptr, uint32_t *hist0 = nullptr);
+hipError_t launch_score(const int32_t *tags, const ScoreArgs &a, const ScoreWorkspace &ws, bool vec_ok,
+                        hipStream_t stream);
 
 // ---- select ----------------------------------------------------------------
 constexpr int kSelectThreads = 1024;
@@ -150,8 +188,10 @@ hipError_t launch_key_minmax(const double *score, int64_t n, const WideWs &w, hi
 // writes mmin/mmax and clears hist).
 hipError_t launch_wide_cut(const double *score, int64_t n, int64_t budget, const WideWs &w, hipStream_t stream);
 
-// keep[i] <- 0 for the `budget` first trajectories in (score desc, id asc).
-// With parts.cnt non-null, also writes the block partials of the keep flags.
+// launch_rank: keep[i] <- 0 for the `budget` first trajectories in (score desc,
+// id asc). With parts.cnt non-null, also writes the block partials of the keep
+// flags. With join.cap, reads the scores from join.ws and finishes the
+// trajectories that were summed in pieces: their scores, S and T.
 // Group means of pace_group_score formed inside the rank over groups (at
 // most kRankMaxN groups): group scores and group keep flags in one launch.
 // Every rank workgroup (one per kRankQ groups) reads all member scores, so
@@ -160,10 +200,11 @@ hipError_t launch_wide_cut(const double *score, int64_t n, int64_t budget, const
 constexpr int kRankQ = 16;              // targets per rank workgroup
 constexpr int64_t kGroupRankLoads = (int64_t)1 << 21;
 hipError_t launch_group_rank(const double *score, int64_t n, const int64_t *group_offsets, int64_t ng,
-                             int64_t budget, double *group_score, uint8_t *group_keep, hipStream_t stream);
+                             int64_t budget, double *group_score, uint8_t *group_keep, hipStream_t stream,
+                             const ScoreJoin &join);
 hipError_t launch_rank(const double *score, int64_t n, int64_t budget, uint8_t *keep,
                        const int64_t *offsets, int64_t n_tokens, const PieceParts &parts,
-                       hipStream_t stream);
+                       hipStream_t stream, const ScoreJoin &join = {});
 size_t select_ws_bytes(int64_t n);
 // Every workgroup finds the cut of the `budget` highest from the level-0
 // histogram and digits, then classifies its trajectories (keep flags, block
@@ -236,8 +277,11 @@ hipError_t launch_filter_step(const int32_t *tags, const int64_t *offsets, int64
                               hipStream_t stream);
 
 // ---- group-level admission ---------------------------------------------------
+// With join.cap, launch_group_score and launch_group_rank read the scores from
+// join.ws and join what they meet; the kernel that expands the group flags
+// writes the joined trajectories' scores, S and T.
 hipError_t launch_group_score(const double *score, int64_t n, const int64_t *group_offsets, int64_t ng,
-                              double *group_score, hipStream_t stream);
+                              double *group_score, hipStream_t stream, const ScoreJoin &join = {});
 hipError_t launch_group_expand(const int64_t *group_offsets, int64_t ng, int64_t n, const uint8_t *group_keep,
                                uint8_t *keep, hipStream_t stream);
 hipError_t launch_group_validate(const int64_t *group_offsets, int64_t ng, int64_t n, int32_t *err,
@@ -256,11 +300,14 @@ hipError_t launch_group_filter_step(const int32_t *tags, const int64_t *offsets,
 // ---- streaming admission rule ------------------------------------------------
 constexpr int64_t kStreamWindowMax = 1024;   // largest score window (ring entries)
 // With offsets and parts.cnt non-null, the draw also writes the compaction's
-// block partials of its keep flags (offsets clamped to [0, n_tokens]).
+// block partials of its keep flags (offsets clamped to [0, n_tokens]). With
+// join.cap, the cutoff's launch also finishes the trajectories that were summed
+// in pieces.
 hipError_t launch_stream_admit(const double *score, int64_t n, double rate, int64_t window_min, int64_t B,
                                double *ring, int64_t cap, int64_t *state, uint8_t *status, uint8_t *keep,
                                int32_t *reject_ids, double *kappa, int64_t *counts, const int64_t *offsets,
-                               int64_t n_tokens, const PieceParts &parts, hipStream_t stream);
+                               int64_t n_tokens, const PieceParts &parts, hipStream_t stream,
+                               const ScoreJoin &join = {});
 
 // ---- Prefix Forgetting Score --------------------------------------------------
 hipError_t launch_prefix_score(const float *lp_new, const float *lp_beh, const int32_t *tags,

@@ -188,10 +188,10 @@ int pace_score(const int32_t *tags, const int64_t *offsets, int64_t n_traj, int6
     const int64_t wmin = p.window_min > 1 ? p.window_min : 1;
     const bool use_prefix = prefix_score != nullptr && window_n >= wmin;
     const ScoreWorkspace ws = score_ws_carve(workspace, n_traj, n_tokens);
-    return hip_status(launch_score(tags, offsets, n_traj, n_tokens, completion, current_version,
-                                   prefix_score, window_sorted, window_n, use_prefix, p.w_wait,
-                                   p.gamma, score_out, gen_sum_out, gen_count_out, ws,
-                                   aligned(tags, 16), (hipStream_t)stream));
+    return hip_status(launch_score(tags, ScoreArgs{offsets, n_traj, n_tokens, completion, current_version,
+                                                   use_prefix ? 1 : 0, p.gamma, prefix_score, window_sorted, window_n,
+                                                   p.w_wait, score_out, gen_sum_out, gen_count_out},
+                                   ws, aligned(tags, 16), (hipStream_t)stream));
 }
 
 static int budget_impl(int64_t occupancy, int64_t capacity, const pace_params *params,
@@ -488,9 +488,11 @@ int pace_stream_step(const int32_t *tags, const int64_t *offsets, int64_t n_traj
     const ScoreWorkspace sws = score_ws_carve(w, n_traj, n_tokens);
     void *cws = w + align256(score_ws_bytes(n_traj, n_tokens));
     hipStream_t st = (hipStream_t)stream;
-    hipError_t e = launch_score(tags, offsets, n_traj, n_tokens, completion, current_version, prefix_score,
-                                window_sorted, window_n, use_prefix, p.w_wait, p.gamma, score_out, gen_sum_out,
-                                gen_count_out, sws, aligned(tags, 16), st);
+    ScoreJoin join;
+    hipError_t e = launch_score_unjoined(tags, ScoreArgs{offsets, n_traj, n_tokens, completion, current_version,
+                                                         use_prefix ? 1 : 0, p.gamma, prefix_score, window_sorted,
+                                                         window_n, p.w_wait, score_out, gen_sum_out, gen_count_out},
+                                         sws, aligned(tags, 16), st, &join);
     // Pools the piece compaction takes get their block partials from the
     // draw itself; the kept trajectories are at most min(batch_size, n).
     const bool pieces = compact_piece_ok(n_traj, n_tokens);
@@ -499,7 +501,7 @@ int pace_stream_step(const int32_t *tags, const int64_t *offsets, int64_t n_traj
         const double rate = r_hat < p.r_max ? r_hat : p.r_max;
         e = launch_stream_admit(score_out, n_traj, rate, p.window_min, batch_size, window_ring, window_cap,
                                 window_state, status_out, keep_out, reject_ids_out, kappa_out, counts_out,
-                                pieces ? offsets : nullptr, n_tokens, pieces ? cw.parts : PieceParts{}, st);
+                                pieces ? offsets : nullptr, n_tokens, pieces ? cw.parts : PieceParts{}, st, join);
     }
     if (e == hipSuccess) {
         if (pieces)

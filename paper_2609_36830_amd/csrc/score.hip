@@ -445,26 +445,7 @@ __global__ __launch_bounds__(kFinT) void score_finalize_kernel(
         if (gen_count) gen_count[i] = r.T;
         key = score_key(r.score);
     }
-    if constexpr (kMinMax) {
-        if (blockIdx.x == 0)
-            for (int b = threadIdx.x; b < (1 << kCutBits); b += kFinT) hist0[b] = 0u;
-        __shared__ uint64_t wl[kFinT / kWave], wh[kFinT / kWave];
-        const uint64_t lo = wave_min_u64(in ? key : ~0ull), hi = wave_max_u64(key);
-        if (lane_id() == 0) {
-            wl[threadIdx.x / kWave] = lo;
-            wh[threadIdx.x / kWave] = hi;
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            uint64_t a = ~0ull, b = 0;
-            for (int w = 0; w < kFinT / kWave; ++w) {
-                a = wl[w] < a ? wl[w] : a;
-                b = wh[w] > b ? wh[w] : b;
-            }
-            mmin[blockIdx.x] = a;
-            mmax[blockIdx.x] = b;
-        }
-    }
+    if constexpr (kMinMax) key_extremes(key, in, mmin, mmax, hist0);
 }
 
 }  // namespace
@@ -478,6 +459,7 @@ ScoreWorkspace score_ws_carve(void *ws, int64_t n, int64_t n_tokens) {
     const int64_t ch = score_max_chunks(n_tokens);
     char *p = (char *)ws;
     ScoreWorkspace w;
+    w.traj = (double *)p;
     w.part_sum = (uint64_t *)p;  p += align256((size_t)n * 8);
     w.part_cnt = (int64_t *)p;   p += align256((size_t)n * 8);
     w.carry_sum = (uint64_t *)p; p += align256((size_t)ch * 8);
@@ -532,16 +514,26 @@ hipError_t launch_score_finalize(const int64_t *offsets, int64_t n, int64_t n_to
 #undef PACE_FIN
 }
 
-hipError_t launch_score(const int32_t *tags, const int64_t *offsets, int64_t n, int64_t n_tokens,
-                        const int32_t *completion, int32_t V, const double *prefix,
-                        const double *window, int64_t W, bool use_prefix, double w_wait, int gamma,
-                        double *score, int64_t *gen_sum, int64_t *gen_count,
-                        const ScoreWorkspace &ws, bool vec_ok, hipStream_t stream) {
+hipError_t launch_score_unjoined(const int32_t *tags, const ScoreArgs &a, const ScoreWorkspace &ws, bool vec_ok,
+                                 hipStream_t stream, ScoreJoin *join) {
+    *join = ScoreJoin{};
+    if (score_by_traj(a.n, a.NT)) {
+        const int64_t cap = score_traj_cap(a.n, a.NT);
+        if (a.NT > cap) *join = ScoreJoin{a, ws, cap};
+        return launch_score_traj(tags, a, ws, stream);
+    }
     int64_t chunk_len = 0;
-    hipError_t e = launch_score_reduce(tags, offsets, n, n_tokens, V, ws, vec_ok, stream, &chunk_len);
+    hipError_t e = launch_score_reduce(tags, a.off, a.n, a.NT, a.V, ws, vec_ok, stream, &chunk_len);
     if (e != hipSuccess) return e;
-    return launch_score_finalize(offsets, n, n_tokens, completion, V, prefix, window, W, use_prefix,
-                                 w_wait, gamma, chunk_len, score, gen_sum, gen_count, ws, stream);
+    return launch_score_finalize(a.off, a.n, a.NT, a.completion, a.V, a.prefix, a.window, a.W, a.use_prefix != 0,
+                                 a.w_wait, a.gamma, chunk_len, a.score, a.gen_sum, a.gen_count, ws, stream);
+}
+
+hipError_t launch_score(const int32_t *tags, const ScoreArgs &a, const ScoreWorkspace &ws, bool vec_ok,
+                        hipStream_t stream) {
+    ScoreJoin join;
+    const hipError_t e = launch_score_unjoined(tags, a, ws, vec_ok, stream, &join);
+    return e != hipSuccess || join.cap == 0 ? e : launch_score_join(a, ws, stream);
 }
 
 }  // namespace pace

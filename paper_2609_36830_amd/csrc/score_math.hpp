@@ -11,6 +11,7 @@
 #pragma once
 
 #include "device_util.hpp"
+#include "kernels.hpp"
 
 #pragma clang fp contract(off)
 
@@ -73,10 +74,18 @@ __device__ __forceinline__ TrajPieces gather_pieces(
     return p;
 }
 
-// Score of one trajectory from its pieces.
-__device__ __forceinline__ TrajScore score_from_pieces(
-    TrajPieces pc, int64_t c, int32_t V, bool use_prefix, double s_pre, const double *win, int64_t W,
-    double w_wait, int gamma) {
+// Prefix weight F from a = #{w in window : w <= s_pre}.
+__device__ __forceinline__ double prefix_weight(int64_t a, int64_t W, int gamma) {
+    int64_t A = 1, B = 1;
+    for (int g = 0; g < gamma; ++g) {
+        A *= a;
+        B *= (W - a);
+    }
+    return (double)A / (double)(A + B);
+}
+
+// Score of one trajectory from its sums and prefix weight.
+__device__ __forceinline__ TrajScore score_from_weight(TrajPieces pc, int64_t c, int32_t V, double F, double w_wait) {
     const uint64_t sp = pc.sp;
     const int64_t T = pc.T;
     // sp = sum(tag) + T over generated tokens
@@ -86,24 +95,127 @@ __device__ __forceinline__ TrajScore score_from_pieces(
     r.S = c * T - sum_tag;
     const double k_wait = (double)((int64_t)V - c);
     const double k_gen = (T > 0) ? (double)r.S / (double)T : 0.0;
-    double F = 1.0;
-    if (use_prefix && !__builtin_isnan(s_pre)) {
-        int64_t a_lo = 0, a_hi = W;          // count of window entries <= s_pre
-        while (a_lo < a_hi) {
-            const int64_t mid = (a_lo + a_hi) >> 1;
-            if (win[mid] <= s_pre) a_lo = mid + 1; else a_hi = mid;
-        }
-        int64_t A = 1, B = 1;
-        for (int g = 0; g < gamma; ++g) {
-            A *= a_lo;
-            B *= (W - a_lo);
-        }
-        F = (double)A / (double)(A + B);
-    }
     const double wait_term = w_wait * k_wait;
     const double gen_term = F * k_gen;
     r.score = wait_term + gen_term;
     return r;
+}
+
+// Count of the ascending window's entries <= s_pre.
+__device__ __forceinline__ int64_t window_count(const double *win, int64_t W, double s_pre) {
+    int64_t a_lo = 0, a_hi = W;
+    while (a_lo < a_hi) {
+        const int64_t mid = (a_lo + a_hi) >> 1;
+        if (win[mid] <= s_pre) a_lo = mid + 1; else a_hi = mid;
+    }
+    return a_lo;
+}
+
+// Score of one trajectory from its pieces.
+__device__ __forceinline__ TrajScore score_from_pieces(
+    TrajPieces pc, int64_t c, int32_t V, bool use_prefix, double s_pre, const double *win, int64_t W,
+    double w_wait, int gamma) {
+    const bool with_f = use_prefix && !__builtin_isnan(s_pre);
+    return score_from_weight(pc, c, V, with_f ? prefix_weight(window_count(win, W, s_pre), W, gamma) : 1.0, w_wait);
+}
+
+// ---- scores formed by trajectory (score_traj.hip) ----------------------------
+// A trajectory of more than cap tokens, starting in tokens [k cap, (k + 1) cap),
+// is summed in np pieces of cap tokens. Its entry of ws.traj is join_mark(k, np)
+// (a NaN, which no score is), and carry slots hold: 4 k its first piece's sums,
+// 4 (k + p) + 1 those of piece p >= 1, 4 k + 2 the prefix weight F and the
+// completion version. (Two such trajectories cannot start within cap tokens, so
+// no slot is used twice.) A reader that meets the mark needs one round trip:
+// with the slots found through the offsets and F through a search of the window
+// it took five, and 24 such trajectories among 3750 cost the rank 8 us.
+constexpr int kJoinSlots = 4;
+constexpr uint64_t kJoinMark = 0x7ffc000000000000ull;
+__device__ __forceinline__ double join_mark(int64_t k, int64_t np) {
+    return __longlong_as_double((long long)(kJoinMark | ((uint64_t)k << 24) | (uint64_t)np));
+}
+__device__ __forceinline__ bool is_join_mark(double s) {
+    return ((uint64_t)__double_as_longlong(s) >> 48) == (kJoinMark >> 48);
+}
+
+__device__ inline TrajScore joined_score(double mark, const ScoreJoin &j) {
+    const uint64_t m = (uint64_t)__double_as_longlong(mark);
+    const int64_t k = (int64_t)((m >> 24) & 0xffffff), np = (int64_t)(m & 0xffffff);
+    const uint64_t *__restrict__ cs = j.ws.carry_sum;
+    const int64_t *__restrict__ cc = j.ws.carry_cnt;
+    const double F = __longlong_as_double((long long)cs[kJoinSlots * k + 2]);
+    const int64_t c = cc[kJoinSlots * k + 2];
+    TrajPieces p{cs[kJoinSlots * k], cc[kJoinSlots * k]};
+    for (int64_t b = 1; b < np; b += kCarryBatch) {
+        uint64_t xs[kCarryBatch];
+        int64_t xc[kCarryBatch];
+#pragma unroll
+        for (int u = 0; u < kCarryBatch; ++u) {
+            const bool in = b + u < np;
+            xs[u] = in ? cs[kJoinSlots * (k + b + u) + 1] : 0;
+            xc[u] = in ? cc[kJoinSlots * (k + b + u) + 1] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < kCarryBatch; ++u) {
+            p.sp += xs[u];
+            p.T += xc[u];
+        }
+    }
+    return score_from_weight(p, c, j.a.V, F, j.a.w_wait);
+}
+
+// Replaces the marks among x by their scores: every lane its first one at a
+// time, so that a wave takes as many round trips as one lane has marks.
+template <int N>
+__device__ __forceinline__ void join_marked(double (&x)[N], const ScoreJoin &j) {
+    while (true) {
+        int at = -1;
+        double m = 0.0;
+#pragma unroll
+        for (int k = N - 1; k >= 0; --k) {
+            if (is_join_mark(x[k])) {
+                at = k;
+                m = x[k];
+            }
+        }
+        if (at < 0) return;
+        const double y = joined_score(m, j).score;
+#pragma unroll
+        for (int k = 0; k < N; ++k) x[k] = k == at ? y : x[k];
+    }
+}
+
+// joined_score of trajectory i, written to its outputs.
+__device__ inline double write_joined(int64_t i, double mark, const ScoreJoin &j) {
+    const TrajScore r = joined_score(mark, j);
+    j.a.score[i] = r.score;
+    if (j.a.gen_sum) j.a.gen_sum[i] = r.S;
+    if (j.a.gen_count) j.a.gen_count[i] = r.T;
+    return r.score;
+}
+
+// The smallest and largest key of a workgroup of kFinGroup trajectories (in:
+// the thread holds one), the range the wide selection histograms; workgroup 0
+// clears that selection's level-0 histogram (hist0).
+__device__ __forceinline__ void key_extremes(uint64_t key, bool in, uint64_t *__restrict__ mmin,
+                                             uint64_t *__restrict__ mmax, uint32_t *__restrict__ hist0) {
+    if (blockIdx.x == 0)
+        for (int b = threadIdx.x; b < (1 << kCutBits); b += kFinGroup) hist0[b] = 0u;
+    __shared__ uint64_t wl[kFinGroup / kWave], wh[kFinGroup / kWave];
+    const uint64_t lo = wave_min_u64(in ? key : ~0ull), hi = wave_max_u64(in ? key : 0ull);
+    if (lane_id() == 0) {
+        wl[threadIdx.x / kWave] = lo;
+        wh[threadIdx.x / kWave] = hi;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint64_t a = ~0ull, b = 0;
+        for (int w = 0; w < kFinGroup / kWave; ++w) {
+            a = wl[w] < a ? wl[w] : a;
+            b = wh[w] > b ? wh[w] : b;
+        }
+        mmin[blockIdx.x] = a;
+        mmax[blockIdx.x] = b;
+    }
 }
 
 }  // namespace pace

@@ -1,0 +1,279 @@
+// pace_score by trajectory for gfx950: one workgroup reads a whole
+// trajectory's tags, sums them and forms its score (Sec. 2 and 3.2, Eq. (1),
+// (2), (6)-(9)), so that no per-chunk pieces go through memory and no second
+// kernel waits for them.
+//
+// HBM-bound, 4 bytes per token. Every thread keeps eight 16-byte loads in
+// flight (each dword-aligned, so a trajectory may start anywhere); a partial
+// batch reads clamped addresses and masks, so no load sits behind a branch.
+// The workgroups of the other trajectories hide one's start (its offsets) and
+// end (the sums over the waves, the window count, two divisions), and the
+// order in which the chip finishes them evens out their lengths. The window
+// entries at or below the prefix score are counted one per thread beside the
+// tags' loads.
+//
+// A trajectory of more than `cap` tokens would leave one workgroup at work
+// alone: its first cap tokens are its workgroup's, and workgroup n + k takes
+// the piece that starts in tokens [k cap, (k + 1) cap), if any: only the
+// trajectory holding token k cap can have one there. Their sums are joined by
+// the kernel that reads the scores next (the rank) or by score_join.
+//
+// Against equal token chunks per wave with the pieces added up by a second
+// kernel, calls back to back: 64 trajectories, 70K tokens 11.0 -> 3.8 us; 1024,
+// 3.8M 11.1 -> 6.6; 2048, 20M 19.0 -> 15.7; 4096, 50.1M 39.9 -> 35.0 us (5.7
+// TB/s).
+#include "device_util.hpp"
+#include "kernels.hpp"
+#include "score_math.hpp"
+
+#pragma clang fp contract(off)
+
+namespace pace {
+
+namespace {
+
+constexpr int kTU = 8;                             // 16-byte loads in flight per thread
+constexpr int64_t kTrajCap = 65536;                // tokens one workgroup of four or eight waves sums, at least
+constexpr int64_t kTrajOverMax = 4096;             // piece workgroups, at most (the cap grows instead)
+constexpr int64_t kTrajFillWaves = 4096;           // waves that few trajectories are spread over
+
+// Sums of one thread: the tags + 1 and the generated tokens.
+struct Narrow {                                    // a thread's tags, each at most V + 1, sum below 2^32
+    uint32_t s = 0, c = 0;
+    __device__ __forceinline__ void add(uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3) {
+        s += x0 + x1 + x2 + x3 + 4u;               // a masked tag (-1) adds 0
+        c += 4u - ((x0 >> 31) + (x1 >> 31) + (x2 >> 31) + (x3 >> 31));
+    }
+};
+struct Wide {
+    uint64_t s = 0;
+    uint32_t c = 0;
+    __device__ __forceinline__ void add(uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3) {
+        const uint32_t u0 = x0 + 1u, u1 = x1 + 1u, u2 = x2 + 1u, u3 = x3 + 1u;
+        s += (uint64_t)u0 + u1 + u2 + u3;
+        c += (u0 != 0u) + (u1 != 0u) + (u2 != 0u) + (u3 != 0u);
+    }
+};
+
+// U vectors of four tags from p on, `stride` tokens apart, of a piece ending
+// at e (at least four tokens long). kLast: vectors may reach past e; they are
+// read from e - 4 and the tokens before p masked.
+template <int U, bool kLast, typename A>
+__device__ __forceinline__ void add_tags(const int32_t *__restrict__ tags, int64_t p, int64_t e, int stride, A &acc) {
+    uint4 x[U];
+    int d[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        int64_t q = p + (int64_t)u * stride;
+        if (kLast) {
+            const int64_t over = q - (e - 4);
+            d[u] = over <= 0 ? 0 : (over < 4 ? (int)over : 4);
+            q = over <= 0 ? q : e - 4;
+        }
+        x[u] = load_a4(tags + q);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (kLast) {
+            x[u].x = d[u] > 0 ? ~0u : x[u].x;
+            x[u].y = d[u] > 1 ? ~0u : x[u].y;
+            x[u].z = d[u] > 2 ? ~0u : x[u].z;
+            x[u].w = d[u] > 3 ? ~0u : x[u].w;
+        }
+        acc.add(x[u].x, x[u].y, x[u].z, x[u].w);
+    }
+}
+
+template <typename A, int kW>
+__global__ __launch_bounds__(kW * kWave) void score_traj_kernel(const int32_t *__restrict__ tags, ScoreArgs a,
+                                                               ScoreWorkspace ws, int64_t cap) {
+    constexpr int kT = kW * kWave;
+    constexpr int kStride = kT * 4;
+    __shared__ uint64_t w_s[kW];
+    __shared__ uint32_t w_c[kW], w_le[kW];
+    const int t = threadIdx.x, lane = lane_id();
+    // The trajectory, and its tokens [p, e) that are this workgroup's.
+    int64_t i = blockIdx.x, p, e, slot = -1, n_pieces = 1;
+    bool whole = true;
+    if (i < a.n) {
+        const int64_t lo = readlane_i64(clamp64(a.off[i], 0, a.NT), 0);
+        const int64_t hi = readlane_i64(clamp64(a.off[i + 1], 0, a.NT), 0);
+        p = lo;
+        e = hi;
+        if (hi - lo > cap) {
+            e = lo + cap;
+            whole = false;
+            slot = kJoinSlots * (lo / cap);
+            n_pieces = (hi - lo + cap - 1) / cap;
+        }
+    } else {
+        // One wave searches: most windows hold no piece, and eight waves'
+        // searches of each cost the 50M-token step 0.2 us.
+        __shared__ int64_t found[3];
+        const int64_t k = i - a.n;
+        if (t < kWave) {
+            int64_t at = wave_last_le(a.off, a.n, k * cap), p0 = 0, e0 = 0;
+            if (at >= 0 && at < a.n) {
+                const int64_t lo = clamp64(a.off[at], 0, a.NT), hi = clamp64(a.off[at + 1], 0, a.NT);
+                if (k * cap > lo) {
+                    p0 = lo + (k * cap - lo + cap - 1) / cap * cap;
+                    e0 = p0 + cap < hi ? p0 + cap : hi;
+                }
+            }
+            if (t == 0) {
+                found[0] = at;
+                found[1] = p0;
+                found[2] = e0;
+            }
+        }
+        __syncthreads();
+        i = readlane_i64(found[0], 0);
+        p = readlane_i64(found[1], 0);
+        e = readlane_i64(found[2], 0);
+        if (p >= e) return;
+        whole = false;
+        slot = kJoinSlots * k + 1;
+    }
+    // Loads that the end of the kernel needs go first.
+    const bool first = whole || (slot % kJoinSlots) == 0;      // holds the trajectory's start
+    const double s_pre = first && a.use_prefix ? a.prefix[i] : __builtin_nan("");
+    const int64_t c = a.completion[i];
+    const bool with_f = !__builtin_isnan(s_pre);
+    uint32_t le = 0;                               // window entries <= s_pre among this thread's
+    if (with_f && a.W <= kWindowLdsMax)
+        for (int64_t x = t; x < a.W; x += kT) le += a.window[x] <= s_pre ? 1u : 0u;
+
+    A acc;
+    if (e - p >= 4) {
+        for (; p + kTU * kStride <= e; p += kTU * kStride) add_tags<kTU, false>(tags, p + t * 4, e, kStride, acc);
+        if (p + 6 * kStride < e) add_tags<8, true>(tags, p + t * 4, e, kStride, acc);
+        else if (p + 4 * kStride < e) add_tags<6, true>(tags, p + t * 4, e, kStride, acc);
+        else if (p + 2 * kStride < e) add_tags<4, true>(tags, p + t * 4, e, kStride, acc);
+        else if (p < e) add_tags<2, true>(tags, p + t * 4, e, kStride, acc);
+    } else if (t < e - p) {
+        acc.add((uint32_t)tags[p + t], ~0u, ~0u, ~0u);
+    }
+    const uint64_t s = wave_sum_u64((uint64_t)acc.s);
+    const uint32_t cn = (uint32_t)readlane_i32((int32_t)wave_incl_scan_u32(acc.c), kWave - 1);
+    const uint32_t ln = with_f ? (uint32_t)readlane_i32((int32_t)wave_incl_scan_u32(le), kWave - 1) : 0u;
+    if (lane == 0) {
+        w_s[t / kWave] = s;
+        w_c[t / kWave] = cn;
+        w_le[t / kWave] = ln;
+    }
+    __syncthreads();
+    if (t != 0) return;
+    TrajPieces pc{0, 0};
+    int64_t at_most = 0;
+#pragma unroll
+    for (int w = 0; w < kW; ++w) {
+        pc.sp += w_s[w];
+        pc.T += (int64_t)w_c[w];
+        at_most += (int64_t)w_le[w];
+    }
+    double F = 1.0;
+    if (with_f) F = prefix_weight(a.W <= kWindowLdsMax ? at_most : window_count(a.window, a.W, s_pre), a.W, a.gamma);
+    if (!whole) {
+        ws.carry_sum[slot] = pc.sp;
+        ws.carry_cnt[slot] = pc.T;
+        if (first) {
+            ws.carry_sum[slot + 2] = (uint64_t)__double_as_longlong(F);
+            ws.carry_cnt[slot + 2] = c;
+            ws.traj[i] = join_mark(slot / kJoinSlots, n_pieces);
+        }
+        return;
+    }
+    const TrajScore r = score_from_weight(pc, c, a.V, F, a.w_wait);
+    ws.traj[i] = r.score;
+    a.score[i] = r.score;
+    if (a.gen_sum) a.gen_sum[i] = r.S;
+    if (a.gen_count) a.gen_count[i] = r.T;
+}
+
+// The carries, one per kScoreChunkMin tokens, hold kJoinSlots per window of
+// cap >= kTrajCap / 4 tokens, the last window's included, once there are more
+// than cap tokens; window and piece numbers fit the mark's 24 bits.
+static_assert(kTrajCap / 4 / kScoreChunkMin >= 2 * kJoinSlots, "carry slots");
+static_assert(kTrajOverMax * 4 < (1 << 24), "window numbers in the mark");
+
+// Trajectories of more than cap tokens; kMinMax as in score_finalize.
+template <bool kMinMax>
+__global__ __launch_bounds__(kFinGroup) void score_join_kernel(ScoreJoin j, uint64_t *__restrict__ mmin,
+                                                              uint64_t *__restrict__ mmax,
+                                                              uint32_t *__restrict__ hist0) {
+    const int64_t i = (int64_t)blockIdx.x * kFinGroup + threadIdx.x;
+    const bool in = i < j.a.n;
+    double s = in ? j.ws.traj[i] : 0.0;
+    if (in && is_join_mark(s)) s = write_joined(i, s, j);
+    if constexpr (kMinMax) key_extremes(score_key(s), in, mmin, mmax, hist0);
+}
+
+}  // namespace
+
+namespace {
+
+// Waves that take a trajectory, from the mean length: enough bytes for each
+// that its start and end (about 3 us) hide under the others' streams, and
+// enough waves for the chip when there are few trajectories. Whole steps, 1 / 2
+// / 4 / 8 waves: 8192 trajectories of 1464 tokens 38.9 / 39.4 / 41.4 / 53.0 us,
+// of 1953 42.0 / 42.2 / 43.4 / 54.5, 8000 of 3500 54.3 / 54.0 / 53.8 / 63.0,
+// 4096 of 6103 42.0 / 41.0 / 39.4 / 41.4, of 12,207 75.7 / 75.0 / 70.6 / 67.1.
+int traj_waves(int64_t n, int64_t n_tokens) {
+    const int64_t mean = n_tokens / n;
+    const int want = mean >= 8192 ? 8 : (mean >= 2560 ? 4 : (mean >= 1536 ? 2 : 1));
+    int fill = 1;
+    while (fill < 8 && fill * 2 * n <= kTrajFillWaves) fill *= 2;
+    return want > fill ? want : fill;
+}
+
+}  // namespace
+
+// Chunks of equal length remain for many short trajectories, where a
+// trajectory does not fill a wave's loads: 16,384 trajectories of 2500 tokens
+// take 75 us a step by chunks and 78 by trajectory, of 3200 90.4 and 89.2, 8200
+// of 5000 69 and 65.
+bool score_by_traj(int64_t n, int64_t n_tokens) { return n <= kRankMaxN || n_tokens / n >= 3072; }
+
+int64_t score_traj_cap(int64_t n, int64_t n_tokens) {
+    if (n == 0) return kTrajCap;
+    const int kw = traj_waves(n, n_tokens);
+    const int64_t least = kw >= 4 ? kTrajCap : kTrajCap / 4 * kw;
+    const int64_t per = n_tokens / kTrajOverMax;
+    return per <= least ? least : (per + least - 1) / least * least;
+}
+
+hipError_t launch_score_traj(const int32_t *tags, const ScoreArgs &a, const ScoreWorkspace &ws, hipStream_t stream) {
+    if (a.n == 0) return hipSuccess;
+    const int kw = traj_waves(a.n, a.NT);
+    const int64_t cap = score_traj_cap(a.n, a.NT);
+    const int64_t over = a.NT > cap ? (a.NT + cap - 1) / cap : 0;
+    const dim3 grid((unsigned)(a.n + over));
+    // Tags are at most V (a precondition), so tag + 1 <= V + 1, and a thread
+    // sums at most cap / (64 kw) of them.
+    const bool narrow = (int64_t)a.V + 1 <= ((((int64_t)1 << 32) - 1) / (cap / (kWave * kw)));
+#define PACE_TRAJ(W)                                                                                              \
+    do {                                                                                                          \
+        if (narrow) return launch(kPhaseReduce, score_traj_kernel<Narrow, W>, grid, dim3((W) * kWave), stream, tags, \
+                                  a, ws, cap);                                                                    \
+        return launch(kPhaseReduce, score_traj_kernel<Wide, W>, grid, dim3((W) * kWave), stream, tags, a, ws, cap); \
+    } while (0)
+    if (kw == 8) PACE_TRAJ(8);
+    if (kw == 4) PACE_TRAJ(4);
+    if (kw == 2) PACE_TRAJ(2);
+    PACE_TRAJ(1);
+#undef PACE_TRAJ
+}
+
+hipError_t launch_score_join(const ScoreArgs &a, const ScoreWorkspace &ws, hipStream_t stream, uint64_t *mmin,
+                             uint64_t *mmax, uint32_t *hist0) {
+    const int64_t cap = score_traj_cap(a.n, a.NT);
+    if (a.n == 0 || (!mmin && a.NT <= cap)) return hipSuccess;
+    const dim3 grid((unsigned)((a.n + kFinGroup - 1) / kFinGroup));
+    if (mmin)
+        return launch(kPhaseFinalize, score_join_kernel<true>, grid, dim3(kFinGroup), stream, ScoreJoin{a, ws, cap},
+                      mmin, mmax, hist0);
+    return launch(kPhaseFinalize, score_join_kernel<false>, grid, dim3(kFinGroup), stream, ScoreJoin{a, ws, cap}, mmin,
+                  mmax, hist0);
+}
+
+}  // namespace pace

@@ -17,6 +17,7 @@
 #include "device_util.hpp"
 #include "kernels.hpp"
 #include "group_math.hpp"
+#include "score_math.hpp"
 #include "select_block.hpp"
 
 namespace pace {
@@ -326,11 +327,15 @@ __device__ __forceinline__ void rank_block(const double (&v)[kKeys], uint64_t kq
 }
 
 
-template <int kKeys>
+// kJoin: score is join.ws.traj of the trajectory scores (score_traj.hip), where the
+// trajectories summed in pieces hold a mark: every workgroup joins those it
+// meets (they are few: each has more than cap tokens), and the one whose
+// targets they are writes their scores, S and T.
+template <int kKeys, bool kJoin>
 __global__ __launch_bounds__(kRankT) void rank_kernel(const double *__restrict__ score, int64_t n,
                                                      int64_t budget, uint8_t *__restrict__ keep,
                                                      const int64_t *__restrict__ off, int64_t NT,
-                                                     PieceParts parts) {
+                                                     PieceParts parts, ScoreJoin join) {
     __shared__ uint32_t part[kRankT / kWave][kRankQ];
     const int t = threadIdx.x;
     const int64_t i0 = (int64_t)blockIdx.x * kRankQ;
@@ -345,11 +350,15 @@ __global__ __launch_bounds__(kRankT) void rank_kernel(const double *__restrict__
     // unit and read out to scalars (a scalar-side conversion branches on
     // every target).
     const int lane = lane_id();
-    const double vq = lane < kRankQ && i0 + lane < n ? score[i0 + lane] : 0.0;
+    double vq = lane < kRankQ && i0 + lane < n ? score[i0 + lane] : 0.0;
     int64_t span = 0;
     if (parts.cnt && t < kRankQ && i0 + t < n) {
         const int64_t lo = clamp64(off[i0 + t], 0, NT), hi = clamp64(off[i0 + t + 1], 0, NT);
         span = hi > lo ? hi - lo : 0;
+    }
+    if constexpr (kJoin) {
+        if (is_join_mark(vq)) vq = t < kRankQ ? write_joined(i0 + lane, vq, join) : joined_score(vq, join).score;
+        join_marked(v, join);
     }
     rank_block<kKeys>(v, score_key(vq), i0, n, budget, keep, span, parts, part);
 }
@@ -360,11 +369,11 @@ __global__ __launch_bounds__(kRankT) void rank_kernel(const double *__restrict__
 // against them, writing the targets' group scores and keep flags. Forming
 // the means in every workgroup costs ng / kRankQ times the loads of one pass
 // over the scores, and saves the group scores' launch.
-template <int kKeys>
+template <int kKeys, bool kJoin>
 __global__ __launch_bounds__(kRankT) void group_rank_kernel(const double *__restrict__ score, int64_t n,
                                                            const int64_t *__restrict__ go, int64_t ng,
                                                            int64_t budget, double *__restrict__ group_score,
-                                                           uint8_t *__restrict__ group_keep) {
+                                                           uint8_t *__restrict__ group_keep, ScoreJoin join) {
     __shared__ uint32_t part[kRankT / kWave][kRankQ];
     __shared__ uint64_t s_key[kRankQ];
     const int t = threadIdx.x;
@@ -375,7 +384,7 @@ __global__ __launch_bounds__(kRankT) void group_rank_kernel(const double *__rest
         const int64_t g = t + (int64_t)u * kRankT;
         v[u] = 0.0;
         if (g < ng) {
-            v[u] = group_mean(score, n, go, g);
+            v[u] = group_mean<kJoin>(score, n, go, g, join);
             if (g >= i0 && g < i0 + kRankQ) {   // this workgroup's targets
                 group_score[g] = v[u];
                 s_key[g - i0] = score_key(v[u]);
@@ -422,13 +431,18 @@ size_t select_ws_bytes(int64_t n) {
 
 hipError_t launch_rank(const double *score, int64_t n, int64_t budget, uint8_t *keep,
                        const int64_t *offsets, int64_t n_tokens, const PieceParts &parts,
-                       hipStream_t stream) {
+                       hipStream_t stream, const ScoreJoin &join) {
     if (n == 0) return hipSuccess;
     if (n > kRankMaxN) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((n + kRankQ - 1) / kRankQ));
-#define PACE_RANK(K) \
-    return launch(kPhaseSelect, rank_kernel<K>, grid, dim3(kRankT), stream, score, n, budget, keep, offsets, \
-                  n_tokens, parts)
+#define PACE_RANK(K)                                                                                                \
+    do {                                                                                                            \
+        if (join.cap)                                                                                               \
+            return launch(kPhaseSelect, rank_kernel<K, true>, grid, dim3(kRankT), stream, (const double *)join.ws.traj, \
+                          n, budget, keep, offsets, n_tokens, parts, join);                                         \
+        return launch(kPhaseSelect, rank_kernel<K, false>, grid, dim3(kRankT), stream, score, n, budget, keep, offsets, \
+                      n_tokens, parts, join);                                                                       \
+    } while (0)
     if (n <= kRankT) PACE_RANK(1);
     if (n <= 2 * kRankT) PACE_RANK(2);
     if (n <= 4 * kRankT) PACE_RANK(4);
@@ -437,13 +451,19 @@ hipError_t launch_rank(const double *score, int64_t n, int64_t budget, uint8_t *
 }
 
 hipError_t launch_group_rank(const double *score, int64_t n, const int64_t *group_offsets, int64_t ng,
-                             int64_t budget, double *group_score, uint8_t *group_keep, hipStream_t stream) {
+                             int64_t budget, double *group_score, uint8_t *group_keep, hipStream_t stream,
+                             const ScoreJoin &join) {
     if (ng == 0) return hipSuccess;
     if (ng > kRankMaxN) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((ng + kRankQ - 1) / kRankQ));
-#define PACE_GROUP_RANK(K) \
-    return launch(kPhaseSelect, group_rank_kernel<K>, grid, dim3(kRankT), stream, score, n, group_offsets, ng, \
-                  budget, group_score, group_keep)
+#define PACE_GROUP_RANK(K)                                                                                     \
+    do {                                                                                                       \
+        if (join.cap)                                                                                          \
+            return launch(kPhaseSelect, group_rank_kernel<K, true>, grid, dim3(kRankT), stream,                \
+                          (const double *)join.ws.traj, n, group_offsets, ng, budget, group_score, group_keep, join); \
+        return launch(kPhaseSelect, group_rank_kernel<K, false>, grid, dim3(kRankT), stream, score, n,          \
+                      group_offsets, ng, budget, group_score, group_keep, join);                               \
+    } while (0)
     if (ng <= kRankT) PACE_GROUP_RANK(1);
     if (ng <= 2 * kRankT) PACE_GROUP_RANK(2);
     if (ng <= 4 * kRankT) PACE_GROUP_RANK(4);

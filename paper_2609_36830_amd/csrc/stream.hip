@@ -24,6 +24,7 @@
 //         of the keep flags are written as well.
 #include "device_util.hpp"
 #include "kernels.hpp"
+#include "score_math.hpp"
 #include "select_block.hpp"
 
 #pragma clang fp contract(off)
@@ -41,8 +42,18 @@ constexpr int kKQ = 16;    // window entries ranked per workgroup
 
 __global__ __launch_bounds__(kST) void stream_kappa_kernel(const double *__restrict__ ring, int64_t cap,
                                                            const int64_t *__restrict__ state, double rate,
-                                                           int64_t window_min, double *__restrict__ kappa_out) {
+                                                           int64_t window_min, double *__restrict__ kappa_out,
+                                                           int64_t n_kappa, ScoreJoin join) {
     static_assert(kStreamWindowMax <= kST, "one window entry per thread");
+    if ((int64_t)blockIdx.x >= n_kappa) {
+        // Beside the cutoff: the trajectories that were summed in pieces.
+        const int64_t i = ((int64_t)blockIdx.x - n_kappa) * kST + threadIdx.x;
+        if (i < join.a.n) {
+            const double m = join.ws.traj[i];
+            if (is_join_mark(m)) write_joined(i, m, join);
+        }
+        return;
+    }
     __shared__ uint32_t part[kSNW][kKQ / 4];
     const int t = threadIdx.x, lane = lane_id(), wave = t / kWave;
     const int64_t head = clamp64(state[0], 0, cap - 1);
@@ -230,9 +241,11 @@ __global__ __launch_bounds__(kST) void stream_admit_kernel(
 hipError_t launch_stream_admit(const double *score, int64_t n, double rate, int64_t window_min, int64_t B,
                                double *ring, int64_t cap, int64_t *state, uint8_t *status, uint8_t *keep,
                                int32_t *reject_ids, double *kappa, int64_t *counts, const int64_t *offsets,
-                               int64_t n_tokens, const PieceParts &parts, hipStream_t stream) {
-    hipError_t e = launch(kPhaseAux, stream_kappa_kernel, dim3((unsigned)((cap + kKQ - 1) / kKQ)), dim3(kST), stream,
-                          ring, cap, state, rate, window_min, kappa);
+                               int64_t n_tokens, const PieceParts &parts, hipStream_t stream,
+                               const ScoreJoin &join) {
+    const int64_t n_kappa = (cap + kKQ - 1) / kKQ, n_join = join.cap ? (n + kST - 1) / kST : 0;
+    hipError_t e = launch(kPhaseAux, stream_kappa_kernel, dim3((unsigned)(n_kappa + n_join)), dim3(kST), stream, ring,
+                          cap, state, rate, window_min, kappa, n_kappa, join);
     if (e != hipSuccess) return e;
     const bool with_parts = offsets && parts.cnt;
     const bool vec = ((uintptr_t)score & 15) == 0 && (!with_parts || ((uintptr_t)offsets & 15) == 0);
