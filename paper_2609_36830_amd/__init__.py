@@ -70,10 +70,31 @@ def _dev(t: torch.Tensor, dtype, name: str) -> torch.Tensor:
     return t
 
 
+# The current stream's handle by device index, without building a Stream object
+# (0.2 us a call in place of 2.0).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(device: torch.device, stream=None) -> int:
     if stream is None:
+        if _raw_stream is not None and device.index is not None:
+            return _raw_stream(device.index)
         stream = torch.cuda.current_stream(device)
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+
+
+def _first(t: torch.Tensor, k: int) -> torch.Tensor:
+    """The first k entries of a 1-d buffer (the buffer itself when it has k)."""
+    return t if t.shape[0] == k else t[:k]
+
+
+def _col_args(cols, cols_out):
+    """The payload columns as the C ABI takes them: arrays of input pointers,
+    element sizes and output pointers."""
+    nc = len(cols)
+    ptrs, sizes = ctypes.c_void_p * max(nc, 1), ctypes.c_int32 * max(nc, 1)
+    return (nc, ptrs(*[c.data_ptr() for c in cols]), sizes(*[c.element_size() for c in cols]),
+            ptrs(*[c.data_ptr() for c in cols_out]))
 
 
 def pace_workspace_bytes(which: int, n_traj: int, n_tokens: int) -> int:
@@ -84,9 +105,9 @@ def pace_workspace_bytes(which: int, n_traj: int, n_tokens: int) -> int:
 
 
 def _workspace(which, n, nt, device, ws):
-    need = pace_workspace_bytes(which, n, nt)
+    """The caller's workspace (the library checks its size), or a new one."""
     if ws is None:
-        ws = torch.empty(max(need, 256), dtype=torch.uint8, device=device)
+        ws = torch.empty(max(pace_workspace_bytes(which, n, nt), 256), dtype=torch.uint8, device=device)
     return ws
 
 
@@ -174,10 +195,7 @@ def pace_compact(offsets, keep, cols: Sequence[torch.Tensor], cols_out=None, off
     if n_kept_tokens_out is None:
         n_kept_tokens_out = torch.empty(1, dtype=torch.int64, device=dev)
     ws = _workspace(WS_COMPACT, n, n_tokens, dev, workspace)
-    nc = len(cols)
-    cin = (ctypes.c_void_p * max(nc, 1))(*[c.data_ptr() for c in cols])
-    cout = (ctypes.c_void_p * max(nc, 1))(*[c.data_ptr() for c in cols_out])
-    eb = (ctypes.c_int32 * max(nc, 1))(*[c.element_size() for c in cols])
+    nc, cin, eb, cout = _col_args(cols, cols_out)
     _check(lib().pace_compact(_ptr(offsets), n, int(n_tokens), _ptr(keep), nc, cin, eb, cout,
                               _ptr(offsets_out), _ptr(kept_ids_out), _ptr(n_kept_tokens_out),
                               _ptr(ws), ws.numel(), _stream(dev, stream)), "pace_compact")
@@ -212,22 +230,9 @@ def pace_filter_step(tags, offsets, completion, current_version, occupancy, capa
     """One whole filter step (Algorithm 1). Returns a dict with budget, r_hat and
     the outputs of pace_score / pace_select / pace_compact (full-capacity tensors;
     reject_ids is cut to the budget)."""
-    _dev(tags, torch.int32, "tags")
-    _dev(offsets, torch.int64, "offsets")
-    _dev(completion, torch.int32, "completion")
-    n = offsets.numel() - 1
-    nt = tags.numel()
-    dev = tags.device
-    W = 0
-    if prefix_score is not None:
-        _dev(prefix_score, torch.float64, "prefix_score")
-    if window_sorted is not None:
-        _dev(window_sorted, torch.float64, "window_sorted")
-        W = window_sorted.numel()
     cols = list(cols)
-    for k, c in enumerate(cols):
-        if not c.is_cuda or not c.is_contiguous() or c.numel() != nt:
-            raise ValueError("column %d must be a contiguous device tensor of n_tokens elements" % k)
+    _filter_step_inputs(tags, offsets, completion, prefix_score, window_sorted, cols)
+    n, dev = offsets.numel() - 1, tags.device
     e = lambda k, dt: torch.empty(k, dtype=dt, device=dev)
     score_out = e(n, torch.float64) if score_out is None else score_out
     if with_counts:
@@ -239,27 +244,49 @@ def pace_filter_step(tags, offsets, completion, current_version, occupancy, capa
     offsets_out = e(n + 1, torch.int64) if offsets_out is None else offsets_out
     kept_ids_out = e(max(n, 1), torch.int32) if kept_ids_out is None else kept_ids_out
     n_kept_tokens_out = e(1, torch.int64) if n_kept_tokens_out is None else n_kept_tokens_out
-    nc = len(cols)
-    cin = (ctypes.c_void_p * max(nc, 1))(*[c.data_ptr() for c in cols])
-    cout = (ctypes.c_void_p * max(nc, 1))(*[c.data_ptr() for c in cols_out])
-    eb = (ctypes.c_int32 * max(nc, 1))(*[c.element_size() for c in cols])
+    b, r_hat = _filter_step_call(tags, offsets, completion, current_version, occupancy, capacity, cols, prefix_score,
+                                 window_sorted, params, r_hat_prev, score_out, gen_sum_out, gen_count_out, keep_out,
+                                 reject_ids_out, cols_out, offsets_out, kept_ids_out, n_kept_tokens_out, workspace,
+                                 stream, _noalloc)
+    return dict(budget=b, r_hat=r_hat, score=score_out, gen_sum=gen_sum_out, gen_count=gen_count_out, keep=keep_out,
+                reject_ids=reject_ids_out[:b], offsets_out=offsets_out, kept_ids=kept_ids_out,
+                n_kept_tokens=n_kept_tokens_out, cols_out=cols_out)
+
+
+def _filter_step_inputs(tags, offsets, completion, prefix_score, window_sorted, cols):
+    _dev(tags, torch.int32, "tags")
+    _dev(offsets, torch.int64, "offsets")
+    _dev(completion, torch.int32, "completion")
+    if prefix_score is not None:
+        _dev(prefix_score, torch.float64, "prefix_score")
+    if window_sorted is not None:
+        _dev(window_sorted, torch.float64, "window_sorted")
+    nt = tags.numel()
+    for k, c in enumerate(cols):
+        if not c.is_cuda or not c.is_contiguous() or c.numel() != nt:
+            raise ValueError("column %d must be a contiguous device tensor of n_tokens elements" % k)
+
+
+def _filter_step_call(tags, offsets, completion, current_version, occupancy, capacity, cols, prefix, window, params,
+                      r_hat_prev, score_out, gen_sum_out, gen_count_out, keep_out, reject_ids_out, cols_out,
+                      offsets_out, kept_ids_out, n_kept_tokens_out, workspace, stream, noalloc=False):
+    """The C call on checked inputs and given outputs. Returns (budget, r_hat)."""
+    n, nt, dev = offsets.numel() - 1, tags.numel(), tags.device
+    nc, cin, eb, cout = _col_args(cols, cols_out)
     rh = ctypes.c_double(float(r_hat_prev))
     b = ctypes.c_int64(0)
-    args = (_ptr(tags), _ptr(offsets), n, nt, _ptr(completion), int(current_version),
-            _ptr(prefix_score), _ptr(window_sorted), W, int(occupancy), int(capacity),
-            ctypes.byref(params) if params is not None else None,
-            ctypes.byref(rh), ctypes.byref(b), _ptr(score_out), _ptr(gen_sum_out),
-            _ptr(gen_count_out), _ptr(keep_out), _ptr(reject_ids_out), nc, cin, eb,
-            cout, _ptr(offsets_out), _ptr(kept_ids_out), _ptr(n_kept_tokens_out))
-    if _noalloc:
+    args = (tags.data_ptr(), offsets.data_ptr(), n, nt, completion.data_ptr(), int(current_version),
+            _ptr(prefix), _ptr(window), 0 if window is None else window.numel(), int(occupancy), int(capacity),
+            None if params is None else ctypes.byref(params), ctypes.byref(rh), ctypes.byref(b),
+            score_out.data_ptr(), _ptr(gen_sum_out), _ptr(gen_count_out), keep_out.data_ptr(),
+            reject_ids_out.data_ptr(), nc, cin, eb, cout, offsets_out.data_ptr(), kept_ids_out.data_ptr(),
+            n_kept_tokens_out.data_ptr())
+    if noalloc:
         _check(lib().pace_filter_step_noalloc(*args, _stream(dev, stream)), "pace_filter_step_noalloc")
     else:
         ws = _workspace(WS_FILTER_STEP, n, nt, dev, workspace)
-        _check(lib().pace_filter_step(*args, _ptr(ws), ws.numel(), _stream(dev, stream)), "pace_filter_step")
-    return dict(budget=int(b.value), r_hat=float(rh.value), score=score_out, gen_sum=gen_sum_out,
-                gen_count=gen_count_out, keep=keep_out, reject_ids=reject_ids_out[: int(b.value)],
-                offsets_out=offsets_out, kept_ids=kept_ids_out, n_kept_tokens=n_kept_tokens_out,
-                cols_out=cols_out)
+        _check(lib().pace_filter_step(*args, ws.data_ptr(), ws.numel(), _stream(dev, stream)), "pace_filter_step")
+    return b.value, rh.value
 
 
 def pace_filter_step_noalloc(tags, offsets, completion, current_version, occupancy, capacity, cols, **kw):
@@ -355,18 +382,15 @@ def pace_group_filter_step(tags, offsets, completion, current_version, group_off
             or any(a.numel() < c.numel() or a.dtype != c.dtype or not a.is_contiguous()
                    for a, c in zip(o["cols_out"], cols))):
         raise ValueError("out buffers are too small for this pool, or do not match its columns")
-    score_out, gen_sum_out, gen_count_out = o["score"][:n], o["gen_sum"][:n], o["gen_count"][:n]
+    score_out, gen_sum_out, gen_count_out = _first(o["score"], n), _first(o["gen_sum"], n), _first(o["gen_count"], n)
     group_score_out, group_keep_out = o["group_score"], o["group_keep"]
     reject_group_ids_out = o["reject_group_ids"]
     keep_out = o["keep"]
-    cols_out = [a[:nt] for a in o["cols_out"]]
-    offsets_out, kept_ids_out = o["offsets_out"][: n + 1], o["kept_ids"]
+    cols_out = [_first(a, nt) for a in o["cols_out"]]
+    offsets_out, kept_ids_out = _first(o["offsets_out"], n + 1), o["kept_ids"]
     n_kept_tokens_out = o["n_kept_tokens"]
     ws = _workspace(WS_FILTER_STEP, max(n, ng), nt, dev, workspace)
-    nc = len(cols)
-    cin = (ctypes.c_void_p * max(nc, 1))(*[c.data_ptr() for c in cols])
-    cout = (ctypes.c_void_p * max(nc, 1))(*[c.data_ptr() for c in cols_out])
-    eb = (ctypes.c_int32 * max(nc, 1))(*[c.element_size() for c in cols])
+    nc, cin, eb, cout = _col_args(cols, cols_out)
     rh = ctypes.c_double(float(r_hat_prev))
     b = ctypes.c_int64(0)
     _check(lib().pace_group_filter_step(
@@ -377,8 +401,8 @@ def pace_group_filter_step(tags, offsets, completion, current_version, group_off
         _ptr(reject_group_ids_out), _ptr(keep_out), nc, cin, eb, cout, _ptr(offsets_out), _ptr(kept_ids_out),
         _ptr(n_kept_tokens_out), _ptr(ws), ws.numel(), _stream(dev, stream)), "pace_group_filter_step")
     return dict(budget=int(b.value), r_hat=float(rh.value), score=score_out, gen_sum=gen_sum_out,
-                gen_count=gen_count_out, group_score=group_score_out[:ng], group_keep=group_keep_out[:ng],
-                reject_group_ids=reject_group_ids_out[: int(b.value)], keep=keep_out[:n],
+                gen_count=gen_count_out, group_score=_first(group_score_out, ng), group_keep=_first(group_keep_out, ng),
+                reject_group_ids=reject_group_ids_out[: int(b.value)], keep=_first(keep_out, n),
                 offsets_out=offsets_out, kept_ids=kept_ids_out, n_kept_tokens=n_kept_tokens_out,
                 cols_out=cols_out)
 
@@ -411,7 +435,7 @@ def pace_stream_admit(score, r_hat: float, window: StreamWindow, batch_size: int
                                    int(batch_size), _ptr(window.ring), window.cap, _ptr(window.state),
                                    _ptr(status_out), _ptr(keep_out), _ptr(reject_ids_out), _ptr(kappa_out),
                                    _ptr(counts_out), _stream(dev, stream)), "pace_stream_admit")
-    return status_out[:n], keep_out[:n], reject_ids_out, kappa_out, counts_out
+    return _first(status_out, n), _first(keep_out, n), reject_ids_out, kappa_out, counts_out
 
 
 def stream_step_buffers(n: int, n_tokens: int, col_dtypes: Sequence[torch.dtype], device):
@@ -445,10 +469,7 @@ def pace_stream_step(tags, offsets, completion, current_version, occupancy, capa
         W = window_sorted.numel()
     cols = list(cols)
     b = buffers if buffers is not None else stream_step_buffers(n, nt, [c.dtype for c in cols], dev)
-    nc = len(cols)
-    cin = (ctypes.c_void_p * max(nc, 1))(*[c.data_ptr() for c in cols])
-    cout = (ctypes.c_void_p * max(nc, 1))(*[c.data_ptr() for c in b["cols_out"]])
-    eb = (ctypes.c_int32 * max(nc, 1))(*[c.element_size() for c in cols])
+    nc, cin, eb, cout = _col_args(cols, b["cols_out"])
     rh = ctypes.c_double(float(r_hat_prev))
     ws = b["workspace"]
     _check(lib().pace_stream_step(
@@ -475,7 +496,7 @@ def pace_prefix_score(lp_new, lp_behavior, prefix_offsets, tags=None, cap: int =
     _check(lib().pace_prefix_score(_ptr(lp_new), _ptr(lp_behavior), _ptr(tags), _ptr(prefix_offsets), n,
                                    lp_new.numel(), int(cap), int(min_tokens), _ptr(s_pre_out),
                                    _stream(lp_new.device, stream)), "pace_prefix_score")
-    return s_pre_out[:n]
+    return _first(s_pre_out, n)
 
 
 def pace_stale_k(gen_sum, gen_count, completion, current_version, k: int, keep_out=None, lag_out=None,
@@ -491,7 +512,7 @@ def pace_stale_k(gen_sum, gen_count, completion, current_version, k: int, keep_o
         lag_out = torch.empty(max(n, 1), dtype=torch.float64, device=dev)
     _check(lib().pace_stale_k(_ptr(gen_sum), _ptr(gen_count), _ptr(completion), int(current_version), n, int(k),
                               _ptr(keep_out), _ptr(lag_out), _stream(dev, stream)), "pace_stale_k")
-    return keep_out[:n], (lag_out[:n] if lag_out is not None else None)
+    return _first(keep_out, n), (_first(lag_out, n) if lag_out is not None else None)
 
 
 def pace_diagnostics(score, gen_sum, gen_count, completion, current_version, keep, edges, hist_out=None,
@@ -552,26 +573,25 @@ class FilterStep:
         self.budget = 0
 
     def score_only(self, tags, offsets, completion, V, prefix=None, window=None, stream=None):
-        return pace_score(tags, offsets, completion, V, prefix, window, self.params,
-                          self.score[: self.n], self.gen_sum[: self.n], self.gen_count[: self.n],
-                          self.ws[0], stream)
+        return pace_score(tags, offsets, completion, V, prefix, window, self.params, _first(self.score, self.n),
+                          _first(self.gen_sum, self.n), _first(self.gen_count, self.n), self.ws[0], stream)
 
     def run(self, tags, offsets, completion, V, occupancy, capacity, cols, prefix=None,
             window=None, stream=None, fused=True):
         """fused: one pace_filter_step call; otherwise the four calls in sequence."""
         if fused:
-            r = pace_filter_step(tags, offsets, completion, V, occupancy, capacity, cols, prefix, window,
-                                 self.params, self.r_hat, self.score[: self.n], self.gen_sum[: self.n],
-                                 self.gen_count[: self.n], self.keep[: self.n], self.reject_ids,
-                                 [c[: self.n_tokens] for c in self.cols_out], self.offsets_out,
-                                 self.kept_ids, self.n_kept_tokens, self.ws[3], stream)
-            self.budget, self.r_hat = r["budget"], r["r_hat"]
+            cols = list(cols)
+            _filter_step_inputs(tags, offsets, completion, prefix, window, cols)
+            self.budget, self.r_hat = _filter_step_call(
+                tags, offsets, completion, V, occupancy, capacity, cols, prefix, window, self.params, self.r_hat,
+                self.score, self.gen_sum, self.gen_count, self.keep, self.reject_ids, self.cols_out, self.offsets_out,
+                self.kept_ids, self.n_kept_tokens, self.ws[3], stream)
             return self
         self.score_only(tags, offsets, completion, V, prefix, window, stream)
         self.budget, self.r_hat = pace_budget(occupancy, capacity, self.params, self.r_hat)
-        pace_select(self.score[: self.n], self.budget, self.keep[: self.n], self.reject_ids,
-                    self.ws[1], stream)
-        pace_compact(offsets, self.keep[: self.n], cols, [c[: self.n_tokens] for c in self.cols_out],
+        keep = _first(self.keep, self.n)
+        pace_select(_first(self.score, self.n), self.budget, keep, self.reject_ids, self.ws[1], stream)
+        pace_compact(offsets, keep, cols, [_first(c, self.n_tokens) for c in self.cols_out],
                      self.offsets_out, self.kept_ids, self.n_kept_tokens, self.ws[2], stream,
                      n_tokens=self.n_tokens)
         return self
