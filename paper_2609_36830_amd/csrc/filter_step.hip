@@ -37,7 +37,7 @@ hipError_t launch_filter_step(const int32_t *tags, const int64_t *offsets, int64
                               int gamma, int64_t budget, double *score, int64_t *gen_sum,
                               int64_t *gen_count, uint8_t *keep, int32_t *reject_ids,
                               const CompactCols &cols, int n_cols, int64_t *offsets_out,
-                              int32_t *kept_ids, int64_t *n_kept_tokens, void *ws, bool vec_ok,
+                              int32_t *kept_ids, int64_t *n_kept_tokens, void *ws,
                               hipStream_t stream) {
     char *p = (char *)ws;
     const ScoreWorkspace sws = score_ws_carve(p, n, n_tokens);
@@ -54,18 +54,18 @@ hipError_t launch_filter_step(const int32_t *tags, const int64_t *offsets, int64
     ScoreJoin join{};
     hipError_t e;
     if (rank_path) {
-        e = launch_score_unjoined(tags, sa, sws, vec_ok, stream, &join);
+        e = launch_score_unjoined(tags, sa, sws, stream, &join);
     } else if (wide_path && score_by_traj(n, n_tokens)) {
         e = launch_score_traj(tags, sa, sws, stream);
         if (e == hipSuccess) e = launch_score_join(sa, sws, stream, ww.mmin, ww.mmax, ww.hist);
     } else if (wide_path) {
         int64_t chunk_len = 0;
-        e = launch_score_reduce(tags, offsets, n, n_tokens, V, sws, vec_ok, stream, &chunk_len);
+        e = launch_score_reduce(tags, offsets, n, n_tokens, V, sws, stream, &chunk_len);
         if (e == hipSuccess)
             e = launch_score_finalize(offsets, n, n_tokens, completion, V, prefix, window, W, use_prefix, w_wait, gamma,
                                       chunk_len, score, gen_sum, gen_count, sws, stream, ww.mmin, ww.mmax, ww.hist);
     } else {
-        e = launch_score(tags, sa, sws, vec_ok, stream);
+        e = launch_score(tags, sa, sws, stream);
     }
     if (e != hipSuccess) return e;
     if (wide_path) {

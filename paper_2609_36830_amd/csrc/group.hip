@@ -234,7 +234,7 @@ hipError_t launch_group_filter_step(const int32_t *tags, const int64_t *offsets,
                                     double *group_score, uint8_t *group_keep, int32_t *reject_group_ids,
                                     uint8_t *keep, const CompactCols &cols, int n_cols,
                                     int64_t *offsets_out, int32_t *kept_ids, int64_t *n_kept_tokens,
-                                    void *ws, bool vec_ok, hipStream_t stream) {
+                                    void *ws, hipStream_t stream) {
     // The workspace is a filter-step workspace sized for max(n, ng) entries.
     const int64_t N = n > ng ? n : ng;
     char *p = (char *)ws;
@@ -248,8 +248,8 @@ hipError_t launch_group_filter_step(const int32_t *tags, const int64_t *offsets,
     const ScoreArgs sa{offsets, n, n_tokens, completion, V, use_prefix ? 1 : 0, gamma, prefix, window, W, w_wait,
                        score, gen_sum, gen_count};
     ScoreJoin join{};
-    hipError_t e = fused ? launch_score_unjoined(tags, sa, sws, vec_ok, stream, &join)
-                         : launch_score(tags, sa, sws, vec_ok, stream);
+    hipError_t e = fused ? launch_score_unjoined(tags, sa, sws, stream, &join)
+                         : launch_score(tags, sa, sws, stream);
     if (e != hipSuccess) return e;
     if (fused) {
         // Group scores inside the rank over groups; one kernel for the

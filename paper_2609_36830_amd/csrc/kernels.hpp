@@ -102,7 +102,7 @@ size_t score_ws_bytes(int64_t n, int64_t n_tokens);
 ScoreWorkspace score_ws_carve(void *ws, int64_t n, int64_t n_tokens);
 
 hipError_t launch_score_reduce(const int32_t *tags, const int64_t *offsets, int64_t n,
-                               int64_t n_tokens, int32_t V, const ScoreWorkspace &ws, bool vec_ok,
+                               int64_t n_tokens, int32_t V, const ScoreWorkspace &ws,
                                hipStream_t stream, int64_t *chunk_len_out);
 // With mmin/mmax non-null, also writes the smallest and largest score key
 // of each group of kFinGroup trajectories (the wide selection's range) and
@@ -124,7 +124,7 @@ int64_t score_traj_cap(int64_t n, int64_t n_tokens);
 hipError_t launch_score_traj(const int32_t *tags, const ScoreArgs &a, const ScoreWorkspace &ws, hipStream_t stream);
 // launch_score_traj, or the chunked kernels; *join says what is left to the
 // kernels that read the scores.
-hipError_t launch_score_unjoined(const int32_t *tags, const ScoreArgs &a, const ScoreWorkspace &ws, bool vec_ok,
+hipError_t launch_score_unjoined(const int32_t *tags, const ScoreArgs &a, const ScoreWorkspace &ws,
                                  hipStream_t stream, ScoreJoin *join);
 // Scores, S and T of the trajectories of more than score_traj_cap tokens; with
 // mmin/mmax non-null the key extremes and the cleared hist0 as in
@@ -132,7 +132,7 @@ hipError_t launch_score_unjoined(const int32_t *tags, const ScoreArgs &a, const 
 // and no extremes are asked for.
 hipError_t launch_score_join(const ScoreArgs &a, const ScoreWorkspace &ws, hipStream_t stream,
                              uint64_t *mmin = nullptr, uint64_t *mmax = nullptr, uint32_t *hist0 = nullptr);
-hipError_t launch_score(const int32_t *tags, const ScoreArgs &a, const ScoreWorkspace &ws, bool vec_ok,
+hipError_t launch_score(const int32_t *tags, const ScoreArgs &a, const ScoreWorkspace &ws,
                         hipStream_t stream);
 
 // ---- select ----------------------------------------------------------------
@@ -273,7 +273,7 @@ hipError_t launch_filter_step(const int32_t *tags, const int64_t *offsets, int64
                               int gamma, int64_t budget, double *score, int64_t *gen_sum,
                               int64_t *gen_count, uint8_t *keep, int32_t *reject_ids,
                               const CompactCols &cols, int n_cols, int64_t *offsets_out,
-                              int32_t *kept_ids, int64_t *n_kept_tokens, void *ws, bool vec_ok,
+                              int32_t *kept_ids, int64_t *n_kept_tokens, void *ws,
                               hipStream_t stream);
 
 // ---- group-level admission ---------------------------------------------------
@@ -295,7 +295,7 @@ hipError_t launch_group_filter_step(const int32_t *tags, const int64_t *offsets,
                                     double *group_score, uint8_t *group_keep, int32_t *reject_group_ids,
                                     uint8_t *keep, const CompactCols &cols, int n_cols,
                                     int64_t *offsets_out, int32_t *kept_ids, int64_t *n_kept_tokens,
-                                    void *ws, bool vec_ok, hipStream_t stream);
+                                    void *ws, hipStream_t stream);
 
 // ---- streaming admission rule ------------------------------------------------
 constexpr int64_t kStreamWindowMax = 1024;   // largest score window (ring entries)

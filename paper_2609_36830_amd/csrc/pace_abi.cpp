@@ -191,7 +191,7 @@ int pace_score(const int32_t *tags, const int64_t *offsets, int64_t n_traj, int6
     return hip_status(launch_score(tags, ScoreArgs{offsets, n_traj, n_tokens, completion, current_version,
                                                    use_prefix ? 1 : 0, p.gamma, prefix_score, window_sorted, window_n,
                                                    p.w_wait, score_out, gen_sum_out, gen_count_out},
-                                   ws, aligned(tags, 16), (hipStream_t)stream));
+                                   ws, (hipStream_t)stream));
 }
 
 static int budget_impl(int64_t occupancy, int64_t capacity, const pace_params *params,
@@ -300,7 +300,7 @@ static int filter_step_impl(const int32_t *tags, const int64_t *offsets, int64_t
                                        prefix_score, window_sorted, window_n, use_prefix, p.w_wait,
                                        p.gamma, budget, score_out, gen_sum_out, gen_count_out,
                                        keep_out, reject_ids_out, cols, n_cols, offsets_out,
-                                       kept_ids_out, n_kept_tokens_out, workspace, aligned(tags, 16),
+                                       kept_ids_out, n_kept_tokens_out, workspace,
                                        (hipStream_t)stream));
     if (rc != PACE_OK) return rc;
     *r_hat_inout = r_hat;
@@ -420,7 +420,7 @@ int pace_group_filter_step(const int32_t *tags, const int64_t *offsets, int64_t 
         tags, offsets, n_traj, n_tokens, completion, current_version, prefix_score, window_sorted, window_n,
         use_prefix, p.w_wait, p.gamma, group_offsets, n_groups, budget, score_out, gen_sum_out, gen_count_out,
         group_score_out, group_keep_out, reject_group_ids_out, keep_out, cols, n_cols, offsets_out, kept_ids_out,
-        n_kept_tokens_out, workspace, aligned(tags, 16), (hipStream_t)stream));
+        n_kept_tokens_out, workspace, (hipStream_t)stream));
     if (rc != PACE_OK) return rc;
     *r_hat_inout = r_hat;
     *budget_out = budget;
@@ -492,7 +492,7 @@ int pace_stream_step(const int32_t *tags, const int64_t *offsets, int64_t n_traj
     hipError_t e = launch_score_unjoined(tags, ScoreArgs{offsets, n_traj, n_tokens, completion, current_version,
                                                          use_prefix ? 1 : 0, p.gamma, prefix_score, window_sorted,
                                                          window_n, p.w_wait, score_out, gen_sum_out, gen_count_out},
-                                         sws, aligned(tags, 16), st, &join);
+                                         sws, st, &join);
     // Pools the piece compaction takes get their block partials from the
     // draw itself; the kept trajectories are at most min(batch_size, n).
     const bool pieces = compact_piece_ok(n_traj, n_tokens);

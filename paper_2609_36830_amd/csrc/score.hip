@@ -97,14 +97,23 @@ __device__ __forceinline__ uint32_t packed(int x) {
     return ((uint32_t)x << 9) + 513u + (uint32_t)(x >> 31);
 }
 
-template <bool kVecLoad, int U>
+// Four tags, dword-aligned: one load wherever the column starts. (Element loads
+// for tags off 16-byte alignment: 17M tags in 20,417 trajectories, a score call
+// 6 us longer.) The launch bound keeps kReduceWavesPerCU waves resident in every
+// arithmetic; without it the 32- and 64-bit ones took 130 to 133 VGPRs, twelve.
+__device__ __forceinline__ int4 load_tags(const int32_t *p) {
+    const uint4 x = load_a4(p);
+    return make_int4((int)x.x, (int)x.y, (int)x.z, (int)x.w);
+}
+
+template <int U>
 __device__ __forceinline__ void load_super(const int32_t *__restrict__ tags, int64_t pos, int64_t ce,
                                            int lane, int4 (&v)[U]) {
 #pragma unroll
     for (int k = 0; k < U; ++k) {
         const int64_t q = pos + (int64_t)k * kWin + (int64_t)lane * kVec;
-        if (kVecLoad && q + kVec <= ce) {
-            v[k] = *reinterpret_cast<const int4 *>(tags + q);
+        if (q + kVec <= ce) {
+            v[k] = load_tags(tags + q);
         } else {
             v[k] = make_int4(-1, -1, -1, -1);      // past the end: masked, adds nothing
             if (q < ce) v[k].x = tags[q];
@@ -115,8 +124,8 @@ __device__ __forceinline__ void load_super(const int32_t *__restrict__ tags, int
     }
 }
 
-template <int kMode, bool kVecLoad, int U = kUnroll>
-__global__ __launch_bounds__(256) void score_reduce_kernel(
+template <int kMode, int U = kUnroll>
+__global__ __launch_bounds__(256, kReduceWavesPerCU / 4) void score_reduce_kernel(
     const int32_t *__restrict__ tags, const int64_t *__restrict__ off, int64_t n, int64_t NT,
     int64_t chunk_len, int64_t n_chunks, uint64_t *__restrict__ part_sum,
     int64_t *__restrict__ part_cnt, uint64_t *__restrict__ carry_sum,
@@ -136,7 +145,7 @@ __global__ __launch_bounds__(256) void score_reduce_kernel(
     // issue them first so the search latency hides under them.
     constexpr int64_t kSuper = (int64_t)kWin * U;
     int4 va[U];
-    load_super<kVecLoad>(tags, cs, ce, lane, va);
+    load_super(tags, cs, ce, lane, va);
 
     // Boundary window: lane k holds B = offsets[bb + k] clamped to [0, NT]
     // (NT past offsets[n]), the start of trajectory bb + k and the end of
@@ -362,8 +371,8 @@ __global__ __launch_bounds__(256) void score_reduce_kernel(
         for (int k = 0; k < kSub; ++k) {
             const int64_t q = p + (int64_t)k * kWin + (int64_t)lane * kVec;
             int4 &x = va[half * kSub + k];
-            if (kVecLoad && q + kVec <= ce) {
-                x = *reinterpret_cast<const int4 *>(tags + q);
+            if (q + kVec <= ce) {
+                x = load_tags(tags + q);
             } else {
                 x = make_int4(-1, -1, -1, -1);
                 if (q < ce) x.x = tags[q];
@@ -468,7 +477,7 @@ ScoreWorkspace score_ws_carve(void *ws, int64_t n, int64_t n_tokens) {
 }
 
 hipError_t launch_score_reduce(const int32_t *tags, const int64_t *offsets, int64_t n,
-                               int64_t n_tokens, int32_t V, const ScoreWorkspace &ws, bool vec_ok,
+                               int64_t n_tokens, int32_t V, const ScoreWorkspace &ws,
                                hipStream_t stream, int64_t *chunk_len_out) {
     // One contiguous, equal token range per resident wave: a single balanced
     // round with no tail of late workgroups.
@@ -479,16 +488,13 @@ hipError_t launch_score_reduce(const int32_t *tags, const int64_t *offsets, int6
     const unsigned grid = (unsigned)((ch + kWavesPerBlock - 1) / kWavesPerBlock);
     // Tags are at most V (a precondition): tag + 1 <= V + 1.
     const int mode = (int64_t)V < (1 << 15) - 1 ? kPacked : ((int64_t)V < (1 << 24) - 1 ? kNarrow : kWideTags);
-#define PACE_REDUCE(MODE, VEC)                                                              \
-    return launch(kPhaseReduce, score_reduce_kernel<MODE, VEC>, dim3(grid), dim3(256), stream, \
+#define PACE_REDUCE(MODE)                                                                \
+    return launch(kPhaseReduce, score_reduce_kernel<MODE>, dim3(grid), dim3(256), stream,    \
                   tags, offsets, n, n_tokens, chunk_len, ch, ws.part_sum, ws.part_cnt,         \
                   ws.carry_sum, ws.carry_cnt)
-    if (mode == kPacked && vec_ok) PACE_REDUCE(kPacked, true);
-    if (mode == kPacked) PACE_REDUCE(kPacked, false);
-    if (mode == kNarrow && vec_ok) PACE_REDUCE(kNarrow, true);
-    if (mode == kNarrow) PACE_REDUCE(kNarrow, false);
-    if (vec_ok) PACE_REDUCE(kWideTags, true);
-    PACE_REDUCE(kWideTags, false);
+    if (mode == kPacked) PACE_REDUCE(kPacked);
+    if (mode == kNarrow) PACE_REDUCE(kNarrow);
+    PACE_REDUCE(kWideTags);
 #undef PACE_REDUCE
 }
 
@@ -514,7 +520,7 @@ hipError_t launch_score_finalize(const int64_t *offsets, int64_t n, int64_t n_to
 #undef PACE_FIN
 }
 
-hipError_t launch_score_unjoined(const int32_t *tags, const ScoreArgs &a, const ScoreWorkspace &ws, bool vec_ok,
+hipError_t launch_score_unjoined(const int32_t *tags, const ScoreArgs &a, const ScoreWorkspace &ws,
                                  hipStream_t stream, ScoreJoin *join) {
     *join = ScoreJoin{};
     if (score_by_traj(a.n, a.NT)) {
@@ -523,16 +529,16 @@ hipError_t launch_score_unjoined(const int32_t *tags, const ScoreArgs &a, const 
         return launch_score_traj(tags, a, ws, stream);
     }
     int64_t chunk_len = 0;
-    hipError_t e = launch_score_reduce(tags, a.off, a.n, a.NT, a.V, ws, vec_ok, stream, &chunk_len);
+    hipError_t e = launch_score_reduce(tags, a.off, a.n, a.NT, a.V, ws, stream, &chunk_len);
     if (e != hipSuccess) return e;
     return launch_score_finalize(a.off, a.n, a.NT, a.completion, a.V, a.prefix, a.window, a.W, a.use_prefix != 0,
                                  a.w_wait, a.gamma, chunk_len, a.score, a.gen_sum, a.gen_count, ws, stream);
 }
 
-hipError_t launch_score(const int32_t *tags, const ScoreArgs &a, const ScoreWorkspace &ws, bool vec_ok,
+hipError_t launch_score(const int32_t *tags, const ScoreArgs &a, const ScoreWorkspace &ws,
                         hipStream_t stream) {
     ScoreJoin join;
-    const hipError_t e = launch_score_unjoined(tags, a, ws, vec_ok, stream, &join);
+    const hipError_t e = launch_score_unjoined(tags, a, ws, stream, &join);
     return e != hipSuccess || join.cap == 0 ? e : launch_score_join(a, ws, stream);
 }
 
