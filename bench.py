@@ -65,10 +65,12 @@ def parse():
 
 
 # (timer phase, kernel) of the fused step's launches: pools of up to 8192
-# trajectories (rank path), and larger ones (level-0 histogram of the cut
+# trajectories (rank path), the tiny pool (ranked and compacted by one kernel),
+# and larger ones (level-0 histogram of the cut
 # search, cut-and-classify, merge-path compaction over blocks of 64
 # trajectories)
 PHASES = ((0, "score_traj"), (2, "rank"), (3, "compact_piece"))
+PHASES_SMALL = ((0, "score_traj"), (3, "compact_piece"))
 PHASES_WIDE = ((0, "score_reduce"), (1, "score_finalize"), (2, "cut_hist"), (6, "classify"),
                (3, "compact_wide"))
 
@@ -264,7 +266,7 @@ def measure_pool(pace, pool, host_cols, mode, K, dev, stream, cus, config_name):
     ms = ev[0].elapsed_time(ev[1]) / K
     assert int(rot.nkt.item()) == n_keep_tok
     # each kernel timed by its own events, same rotation
-    phases = PHASES if pool.n <= 8192 else PHASES_WIDE
+    phases = PHASES_SMALL if pool.n <= 64 else PHASES if pool.n <= 8192 else PHASES_WIDE
     kev = [[(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in phases]
            for _ in range(K)]
     for pairs in kev:

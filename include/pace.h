@@ -115,7 +115,7 @@ int pace_workspace_bytes(int which, int64_t n_traj, int64_t n_tokens, size_t *by
  * is NaN (no prefix score: the rollout was never interrupted), or when
  * window_n < max(params->window_min, 1).
  *
- * tags          int32 [n_tokens], 16-byte aligned for the vector path
+ * tags          int32 [n_tokens]
  * offsets       int64 [n_traj+1]
  * completion    int32 [n_traj]
  * current_version  j; must be < 2^31 - 1
@@ -164,8 +164,10 @@ int pace_select(const double *score, int64_t n_traj, int64_t budget, uint8_t *ke
  *                   elem_bytes[c] in {1,2,4,8} bytes
  * cols_in, cols_out [host] arrays of n_cols device pointers; each output
  *                   column must hold n_tokens elements (the upper bound, so no
- *                   host sync is needed to size it). 16-byte aligned columns
- *                   take the vector path.
+ *                   host sync is needed to size it). Any element-aligned
+ *                   start is read and written in vectors, except beyond 262144
+ *                   trajectories, where columns off 16-byte alignment copy
+ *                   element by element.
  * elem_bytes        [host] int32 [n_cols]
  * offsets_out       int64 [n_traj+1]: entries 0..n_kept hold the packed CSR
  * kept_ids_out      int32 [n_traj]:   entries 0..n_kept-1 hold the kept ids
@@ -192,8 +194,9 @@ int pace_validate(const int32_t *tags, const int64_t *offsets, int64_t n_traj, i
  * three dependent launches instead of five or six: the score kernel; the rank
  * kernel, which also finishes trajectories too long for one workgroup and
  * writes the per-block partials the compaction needs; and the compaction,
- * which writes the rejected ids. Pools of 8192 < n_traj <= 262144 select
- * across the whole device (a level-0 histogram, then a kernel that finds the
+ * which writes the rejected ids (small pools, up to 256 trajectories and a few
+ * hundred thousand kept tokens, select and compact in one). Pools of
+ * 8192 < n_traj <= 262144 select across the whole device (a level-0 histogram, then a kernel that finds the
  * cut and writes the keep flags and partials: five launches); larger pools run
  * the separate calls' kernels.
  *
@@ -412,7 +415,8 @@ int pace_diagnostics(const double *score, const int64_t *gen_sum, const int64_t 
  *   to 8192 trajectories the fused steps have neither), PACE_PHASE_SELECT (the
  *   rank kernel, the single-workgroup select of the largest pools, the streaming draw, or in
  *   pace_group_filter_step the rank over groups),
- *   PACE_PHASE_COMPACT (the compaction copy kernel), PACE_PHASE_PREFIX (the
+ *   PACE_PHASE_COMPACT (the compaction copy kernel; in small filter steps it
+ *   selects too, and there is no select phase), PACE_PHASE_PREFIX (the
  *   Prefix Forgetting Score kernel), PACE_PHASE_AUX (the single kernel of
  *   pace_group_score, pace_group_expand, pace_stale_k or pace_diagnostics,
  *   the window-cutoff kernel of the streaming rule, or in

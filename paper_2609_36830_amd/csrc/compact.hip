@@ -29,6 +29,7 @@
 
 #include "device_util.hpp"
 #include "kernels.hpp"
+#include "score_math.hpp"
 
 namespace pace {
 
@@ -268,6 +269,14 @@ __device__ __forceinline__ void copy_bytes(const char *__restrict__ src, char *_
     if (t == kThreads - 63 && h + nv * 16 != nb) store_a1(dst + nb - 16, load_a1(src + nb - 16));
 }
 
+// A workgroup's part of a span: all its waves together, or a short part by one
+// wave, in turn.
+__device__ __forceinline__ void copy_part(const char *__restrict__ src, char *__restrict__ dst, int64_t nb, int wv,
+                                          int &turn) {
+    if (nb > kWaveCopy) copy_bytes<kPT>(src, dst, nb, (int)threadIdx.x);
+    else if ((turn++ & (kPW - 1)) == wv) copy_bytes<kWave>(src, dst, nb, lane_id());
+}
+
 // The block partials of at most kWave * kPL blocks, kPL consecutive ones per
 // lane, and their exclusive prefix at the lane's first.
 template <typename T, int kPL>
@@ -405,11 +414,7 @@ __global__ __launch_bounds__(kPT) void compact_range_kernel(
             const int64_t dj = readlane_i64(d, j), lj = readlane_i64(len, j), sj = readlane_i64(lo, j);
             const int64_t a = dj > x0 ? dj : x0;
             const int64_t e = dj + lj < x1 ? dj + lj : x1;
-            const int64_t nbytes = (e - a) * E;
-            const char *sp = in + (sj + (a - dj)) * E;
-            char *dp = out + a * E;
-            if (nbytes > kWaveCopy) copy_bytes<kPT>(sp, dp, nbytes, (int)threadIdx.x);
-            else if ((turn++ & (kPW - 1)) == wv) copy_bytes<kWave>(sp, dp, nbytes, lane);
+            copy_part(in + (sj + (a - dj)) * E, out + a * E, (e - a) * E, wv, turn);
         }
         lb += readlane_i64(incl, kWave - 1);
         if (lb >= x1) return;
@@ -423,6 +428,99 @@ __global__ __launch_bounds__(kPT) void compact_range_kernel(
         const uint64_t mm = ballot(nx != INT64_MAX);
         if (!mm) return;
         b = readlane_i64(nx, __ffsll((long long)mm) - 1);
+    }
+}
+
+// Small pools in the filter step: the rank and the range copy in one launch, since a launch costs such a step more than the work
+// (the host 3.7 us, the device 3 to 4). Every workgroup ranks all trajectories,
+// one per thread, against the keys in LDS (rank_i = #{j : key_j > key_i} +
+// #{j < i : key_j == key_i}; of another wave's trajectories all ids lie on one
+// side, so one compare decides), scans the kept spans into a table and copies
+// its range; workgroup 0 writes the keep flags and index outputs, and joins
+// trajectories summed in pieces into their outputs. 64 trajectories, 70K tokens
+// 16.4 -> 13.4 us a step.
+template <bool kJoin>
+__global__ __launch_bounds__(kPT) void rank_compact_small_kernel(
+    const double *__restrict__ score, const int64_t *__restrict__ off, int64_t n, int64_t NT, int64_t budget,
+    int64_t n_rng, uint8_t *__restrict__ keep, CompactCols cols, int n_cols, int64_t *__restrict__ offsets_out,
+    int32_t *__restrict__ kept_ids, int64_t *__restrict__ n_kept_tokens, int32_t *__restrict__ reject_ids,
+    ScoreJoin join) {
+    static_assert(kSmallMaxN == kPT, "one trajectory per thread");
+    __shared__ uint64_t s_key[kPT];
+    __shared__ int64_t s_dst[kPT + 1], s_src[kPT];
+    __shared__ uint32_t w_cnt[kPW];
+    __shared__ int64_t w_len[kPW];
+    const int t = threadIdx.x;
+    const int wv = __builtin_amdgcn_readfirstlane(t / kWave);
+    const bool in = t < n, writer = blockIdx.x == 0 && blockIdx.y == 0;
+    double s = 0.0;
+    int64_t lo = 0, hi = 0;
+    if (in) {
+        s = score[t];
+        lo = clamp64(off[t], 0, NT);
+        hi = clamp64(off[t + 1], 0, NT);
+    }
+    if (kJoin && in && is_join_mark(s)) s = writer ? write_joined(t, s, join) : joined_score(s, join).score;
+    // A number's key is above 0 (-inf's is the smallest), padding is 0.
+    const uint64_t key = in ? score_key(s) : 0ull;
+    s_key[t] = key;
+    __syncthreads();
+    uint32_t r = 0;
+    const int nw = (int)((n + kWave - 1) / kWave);
+    for (int g = 0; g < nw; ++g) {
+        const uint64_t *k = s_key + g * kWave;
+        if (g == wv) {
+            for (int j = 0; j < kWave; ++j) r += (k[j] > key || (k[j] == key && j < lane_id())) ? 1u : 0u;
+        } else {
+            const uint64_t edge = g < wv ? key - 1 : key;
+#pragma unroll 16
+            for (int j = 0; j < kWave; ++j) r += k[j] > edge ? 1u : 0u;
+        }
+    }
+    const bool kept = in && (int64_t)r >= budget;
+    const int64_t len = kept && hi > lo ? hi - lo : 0;
+    uint32_t m;
+    int64_t sum;
+    const int64_t rank = block_excl_sum_u32<kPW>(kept ? 1u : 0u, m, w_cnt);
+    const int64_t dst = block_excl_sum_i64<kPW>(len, sum, w_len);
+    if (kept) {
+        s_dst[rank] = dst;
+        s_src[rank] = lo;
+    }
+    if (t == 0) s_dst[m] = sum;
+    if (writer && in) {
+        keep[t] = kept ? 1 : 0;
+        if (kept) {
+            offsets_out[rank] = dst;
+            kept_ids[rank] = t;
+        } else if (t - rank < budget) {
+            reject_ids[t - rank] = t;
+        }
+    }
+    if (writer && t == 0) {
+        offsets_out[m] = sum;
+        *n_kept_tokens = sum;
+    }
+    __syncthreads();
+    const int64_t total = sum < NT ? sum : NT;   // malformed offsets could overflow the output
+    const int64_t S = ((total + n_rng - 1) / n_rng + 63) / 64 * 64;
+    const int64_t x0 = (int64_t)blockIdx.x * S;
+    if (n_cols == 0 || x0 >= total) return;
+    const int64_t x1 = x0 + S < total ? x0 + S : total;
+    const int col = blockIdx.y;
+    const int64_t E = cols.elem[col];
+    const char *in_c = (const char *)cols.in[col];
+    char *out_c = (char *)cols.out[col];
+    // The last span starting at or before x0.
+    int j = 0;
+    for (int step = kPT / 2; step > 0; step >>= 1)
+        if (j + step < (int)m && readlane_i64(s_dst[j + step], 0) <= x0) j += step;
+    int turn = 0;
+    for (; j < (int)m; ++j) {
+        const int64_t d = readlane_i64(s_dst[j], 0), d1 = readlane_i64(s_dst[j + 1], 0);
+        if (d >= x1) return;
+        const int64_t a = d > x0 ? d : x0, e = d1 < x1 ? d1 : x1;
+        if (a < e) copy_part(in_c + (readlane_i64(s_src[j], 0) + (a - d)) * E, out_c + a * E, (e - a) * E, wv, turn);
     }
 }
 
@@ -844,6 +942,45 @@ hipError_t launch_compact_partials(const int64_t *offsets, int64_t n, int64_t n_
                   offsets, n, n_tokens, keep, parts);
 }
 
+static int64_t expected_kept(int64_t n, int64_t n_tokens, int64_t kept) {
+    return n > 0 ? (int64_t)((double)n_tokens * ((double)kept / (double)n)) : 0;
+}
+
+// Ranges per column. max_kept / n of the tokens is the expected batch: as many
+// ranges as fill the chip once (8 workgroups per CU over all columns) while they
+// hold kRangeMin tokens, up to 12 per CU and column while they hold kRangeLen.
+// Finer ranges even out the workgroups' end times, but each pays its look-up: at
+// 4870 trajectories of 620 tokens and four columns, 2040 workgroups take 2 us
+// less than 3500; at 10M kept tokens and three columns, 2436 to 3072 ranges of a
+// column take 2 us less than 683 and 3 us less than 4096.
+static int64_t range_count(int64_t n, int64_t n_tokens, int n_cols, int64_t max_kept) {
+    const int64_t cus = resident_waves() / 16;
+    const int64_t est = expected_kept(n, n_tokens, max_kept < 0 ? 0 : std::min(max_kept, n));
+    const int64_t fill = std::min(est / kRangeMin, cus * 8 / n_cols);
+    const int64_t fine = std::min(est / kRangeLen, cus * 12);
+    return std::max<int64_t>(std::max(fill, fine), 1);
+}
+
+bool small_step_ok(int64_t n, int64_t n_tokens, int n_cols, int64_t budget) {
+    const int64_t most = kSmallMaxCopy * (n <= kSmallMaxN / 2 ? 2 : 1) / (n_cols > 0 ? n_cols : 1);
+    return n <= kSmallMaxN && expected_kept(n, n_tokens, n - budget) <= most;
+}
+
+hipError_t launch_rank_compact_small(const double *score, const int64_t *offsets, int64_t n, int64_t n_tokens,
+                                     int64_t budget, uint8_t *keep, const CompactCols &cols, int n_cols,
+                                     int64_t *offsets_out, int32_t *kept_ids, int64_t *n_kept_tokens,
+                                     int32_t *reject_ids, hipStream_t stream, const ScoreJoin &join) {
+    if (n > kSmallMaxN) return hipErrorInvalidValue;
+    const int64_t n_rng = n_cols > 0 ? std::max<int64_t>(expected_kept(n, n_tokens, n - budget) / kRangeMin, 1) : 1;
+    const dim3 grid((unsigned)n_rng, (unsigned)(n_cols > 0 ? n_cols : 1));
+    if (join.cap)
+        return launch(kPhaseCompact, rank_compact_small_kernel<true>, grid, dim3(kPT), stream,
+                      (const double *)join.ws.traj, offsets, n, n_tokens, budget, n_rng, keep, cols, n_cols, offsets_out,
+                      kept_ids, n_kept_tokens, reject_ids, join);
+    return launch(kPhaseCompact, rank_compact_small_kernel<false>, grid, dim3(kPT), stream, score, offsets, n, n_tokens,
+                  budget, n_rng, keep, cols, n_cols, offsets_out, kept_ids, n_kept_tokens, reject_ids, join);
+}
+
 hipError_t launch_compact_pieces(const int64_t *offsets, int64_t n, int64_t n_tokens, const uint8_t *keep,
                                  const PieceParts &parts, const CompactCols &cols, int n_cols,
                                  int64_t *offsets_out, int32_t *kept_ids, int64_t *n_kept_tokens,
@@ -853,23 +990,7 @@ hipError_t launch_compact_pieces(const int64_t *offsets, int64_t n, int64_t n_to
     if (blk == kPieceBlock) {
         if (nb > 8 * kWave) return hipErrorInvalidValue;
         const int64_t n_idx = nb > 0 ? (nb + kPW - 1) / kPW : 1;
-        // Ranges per column. max_kept / n of the tokens is the expected batch:
-        // as many ranges as fill the chip once (8 workgroups per CU over all
-        // columns) while they hold kRangeMin tokens, up to 12 per CU and column
-        // while they hold kRangeLen. Finer ranges even out the workgroups' end
-        // times, but each pays its look-up: at 4870 trajectories of 620 tokens
-        // and four columns, 2040 workgroups take 2 us less than 3500; at 10M
-        // kept tokens and three columns, 2436 to 3072 ranges of a column take
-        // 2 us less than 683 and 3 us less than 4096.
-        int64_t n_rng = 0;
-        if (copy && n_cols > 0) {
-            const int64_t cus = resident_waves() / 16;
-            const int64_t kept = max_kept < 0 ? 0 : std::min(max_kept, n);
-            const int64_t est = n > 0 ? (int64_t)((double)n_tokens * ((double)kept / (double)n)) : 0;
-            const int64_t fill = std::min(est / kRangeMin, cus * 8 / n_cols);
-            const int64_t fine = std::min(est / kRangeLen, cus * 12);
-            n_rng = std::max<int64_t>(std::max(fill, fine), 1);
-        }
+        const int64_t n_rng = copy && n_cols > 0 ? range_count(n, n_tokens, n_cols, max_kept) : 0;
         const dim3 grid((unsigned)(n_idx + n_rng), (unsigned)(copy && n_cols > 0 ? n_cols : 1));
 #define PACE_RANGES(P)                                                                                          \
     return launch(kPhaseCompact, compact_range_kernel<P>, grid, dim3(kPT), stream, offsets, n,    \

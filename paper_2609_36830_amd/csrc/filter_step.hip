@@ -12,7 +12,8 @@
 //                                    and column copies it
 //
 // The same results as pace_score, pace_budget, pace_select and pace_compact
-// called in sequence, in three launches. Pools beyond the rank kernel's limit
+// called in sequence, in three launches; in two for small pools
+// (2 and 3 as one kernel, rank_compact_small in compact.hip). Pools beyond the rank kernel's limit
 // (8192 trajectories) take the selection spread over the chip instead of the
 // rank (select_wide.hip): the scores by trajectory or, for short ones, by
 // chunks (score.hip: score_reduce, score_finalize), with per-group key extremes
@@ -79,6 +80,9 @@ hipError_t launch_filter_step(const int32_t *tags, const int64_t *offsets, int64
                                      kept_ids, n_kept_tokens, reject_ids, budget, n_kept, stream, kWideBlock,
                                      true);
     }
+    if (rank_path && small_step_ok(n, n_tokens, n_cols, budget))
+        return launch_rank_compact_small(score, offsets, n, n_tokens, budget, keep, cols, n_cols, offsets_out, kept_ids,
+                                         n_kept_tokens, reject_ids, stream, join);
     if (rank_path) {
         const CompactWs cw = compact_ws_carve(cws_base, n, n_tokens);
         e = launch_rank(score, n, budget, keep, offsets, n_tokens, cw.parts, stream, join);

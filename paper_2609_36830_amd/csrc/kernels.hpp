@@ -261,6 +261,20 @@ hipError_t launch_compact_pieces(const int64_t *offsets, int64_t n, int64_t n_to
                                  int64_t *offsets_out, int32_t *kept_ids, int64_t *n_kept_tokens,
                                  int32_t *reject_ids, int64_t budget, int64_t max_kept,
                                  hipStream_t stream, int blk = kPieceBlock, bool copy = true);
+// Selection and compaction of the filter step in one launch, where
+// small_step_ok (scores as launch_rank takes them; n = 0 included).
+// Every workgroup repeats the ranking, so it is for batches that a few hundred
+// workgroups copy: expected kept tokens times columns up to kSmallMaxCopy, twice
+// that for at most half as many trajectories. Three launches / two, us a step:
+// 64 trajectories, 70K tokens 16.4 / 13.4; 64, 1.5M 16.0 / 14.3; 256, 1M 16.1 /
+// 14.1; 256, 2M 16.0 / 18.2; 256, 1M in three columns 17.0 / 21.3.
+constexpr int64_t kSmallMaxN = 256;
+constexpr int64_t kSmallMaxCopy = (int64_t)1 << 19;
+bool small_step_ok(int64_t n, int64_t n_tokens, int n_cols, int64_t budget);
+hipError_t launch_rank_compact_small(const double *score, const int64_t *offsets, int64_t n, int64_t n_tokens,
+                                     int64_t budget, uint8_t *keep, const CompactCols &cols, int n_cols,
+                                     int64_t *offsets_out, int32_t *kept_ids, int64_t *n_kept_tokens,
+                                     int32_t *reject_ids, hipStream_t stream, const ScoreJoin &join);
 hipError_t launch_compact(const int64_t *offsets, int64_t n, int64_t n_tokens, const uint8_t *keep,
                           const CompactCols &cols, int n_cols, int64_t *offsets_out,
                           int32_t *kept_ids, int64_t *n_kept_tokens, void *ws, hipStream_t stream);
