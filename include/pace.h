@@ -196,9 +196,9 @@ int pace_validate(const int32_t *tags, const int64_t *offsets, int64_t n_traj, i
  * writes the per-block partials the compaction needs; and the compaction,
  * which writes the rejected ids (small pools, up to 256 trajectories and a few
  * hundred thousand kept tokens, select and compact in one). Pools of
- * 8192 < n_traj <= 262144 select across the whole device (a level-0 histogram, then a kernel that finds the
- * cut and writes the keep flags and partials: five launches); larger pools run
- * the separate calls' kernels.
+ * 8192 < n_traj <= 262144 select across the whole device (a level-0 histogram,
+ * then a kernel that finds the cut and writes the keep flags and partials: five
+ * launches); larger pools run the separate calls' kernels.
  *
  * occupancy, capacity, r_hat_inout, budget_out: as pace_budget ([host]).
  * score_out, gen_sum_out, gen_count_out: as pace_score (gen_* may be NULL).

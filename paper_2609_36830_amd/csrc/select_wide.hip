@@ -253,6 +253,28 @@ __device__ void find_cut(const double *__restrict__ score, int64_t n, int64_t bu
         if (t == 0) sm.cut = CutRec{2, lo, 0, 0};
     };
 
+    auto rank_candidates = [&](uint32_t cnt) {
+        // Rank by counting: candidate j gets threads 4j .. 4j + 3, each
+        // comparing it with every fourth candidate; the need-th largest
+        // (key desc, id asc) has rank need - 1.
+        const uint32_t j = (uint32_t)t >> 2, q = (uint32_t)t & 3u;
+        uint32_t r = 0;
+        uint64_t ka = 0;
+        uint32_t ia = 0;
+        if (j < cnt) {
+            ka = sm.ck[j];
+            ia = sm.ci[j];
+            for (uint32_t x = q; x < cnt; x += 4) {
+                const uint64_t kb = sm.ck[x];
+                const uint32_t ib = sm.ci[x];
+                r += (kb > ka || (kb == ka && ib < ia)) ? 1u : 0u;
+            }
+        }
+        r += (uint32_t)__shfl_xor((int)r, 1, kWave);
+        r += (uint32_t)__shfl_xor((int)r, 2, kWave);
+        if (j < cnt && q == 0u && (int64_t)r == need - 1) sm.cut = CutRec{3, ka, (int64_t)ia, 0};
+    };
+
     // Level 0: the global histogram of the level-0 digits, from the top.
     uint32_t d0;
     {
@@ -313,6 +335,15 @@ __device__ void find_cut(const double *__restrict__ score, int64_t n, int64_t bu
         }
         __syncthreads();
         cnt = sm.ncand < (uint32_t)kCandCap ? sm.ncand : (uint32_t)kCandCap;
+        if (cnt <= (uint32_t)kRankMax) {
+            // Few enough to rank at once: the bin's key range (two wave
+            // reductions and a barrier) is not needed. 1.5 us of the
+            // 65,536-trajectory step.
+            if (t < (int)cnt) sm.ck[t] = score_key(score[sm.ci[t]]);
+            __syncthreads();
+            rank_candidates(cnt);
+            return;
+        }
         for (uint32_t j = (uint32_t)t; j < cnt; j += kWT) {
             const uint64_t k = score_key(score[sm.ci[j]]);
             sm.ck[j] = k;
@@ -443,25 +474,7 @@ __device__ void find_cut(const double *__restrict__ score, int64_t n, int64_t bu
     }
 
     if (staged && cnt <= (uint32_t)kRankMax) {
-        // Rank by counting: candidate j gets threads 4j .. 4j + 3, each
-        // comparing it with every fourth candidate; the need-th largest
-        // (key desc, id asc) has rank need - 1.
-        const uint32_t j = (uint32_t)t >> 2, q = (uint32_t)t & 3u;
-        uint32_t r = 0;
-        uint64_t ka = 0;
-        uint32_t ia = 0;
-        if (j < cnt) {
-            ka = sm.ck[j];
-            ia = sm.ci[j];
-            for (uint32_t x = q; x < cnt; x += 4) {
-                const uint64_t kb = sm.ck[x];
-                const uint32_t ib = sm.ci[x];
-                r += (kb > ka || (kb == ka && ib < ia)) ? 1u : 0u;
-            }
-        }
-        r += (uint32_t)__shfl_xor((int)r, 1, kWave);
-        r += (uint32_t)__shfl_xor((int)r, 2, kWave);
-        if (j < cnt && q == 0u && (int64_t)r == need - 1) sm.cut = CutRec{3, ka, (int64_t)ia, 0};
+        rank_candidates(cnt);
         return;
     }
 
