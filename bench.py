@@ -158,28 +158,32 @@ def alg_bytes(pool, n_keep_tok, col_bytes, W, use_prefix=True):
     return b + score_call + select_call + compact_call
 
 
-def reduce_traffic(config, cols):
-    """HBM bytes per score_reduce launch measured with rocprofv3 counters
+def score_traffic(kernel, config, cols):
+    """HBM bytes per launch of the score kernel measured with rocprofv3 counters
     (FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, the factors a plain device copy of
     known size gives), or None when the kernel's sources have changed since
     the counters were taken or no counters exist for this pool."""
     import hashlib
+    rec = SCORE_COUNTERS.get(config) if cols == 1 else None
+    if rec is None or rec["kernel"] != kernel:
+        return None
     h = hashlib.sha256()
-    for f in ("score.hip", "score_math.hpp", "device_util.hpp"):
+    for f in (kernel_source(kernel), "score_math.hpp", "device_util.hpp"):
         with open(os.path.join(ROOT, "paper_2609_36830_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
-    rec = REDUCE_COUNTERS.get(config) if cols == 1 else None
-    if rec is None or rec["sha256"] != h.hexdigest():
-        return None
-    return rec["bytes"]
+    return rec["bytes"] if rec["sha256"] == h.hexdigest() else None
 
 
-# config -> {"sha256": digest of the score_reduce sources, "bytes": HBM bytes per launch}
-REDUCE_COUNTERS = {
-    # profiles/filter_step_hbm_counters.md: FETCH_SIZE 98218.9 KiB, WRITE_SIZE 170.2 KiB
-    "stress": {"sha256": "97cdaed24ff7101054241bfed79d2b19a6fa70afd19992b81495cc102254f5b9", "bytes": 201326592},
-    # profiles/filter_step_hbm_counters.md: FETCH_SIZE 103516.6 KiB, WRITE_SIZE 1139.1 KiB
-    "wide": {"sha256": "97cdaed24ff7101054241bfed79d2b19a6fa70afd19992b81495cc102254f5b9", "bytes": 213168435},
+def kernel_source(kernel):
+    return "score_traj.hip" if kernel == "score_traj" else "score.hip"
+
+
+# config -> the score kernel, the digest of its sources and its HBM bytes per launch
+SCORE_COUNTERS = {
+    # profiles/filter_step_hbm_counters.md: FETCH_SIZE 99050.4 KiB, WRITE_SIZE 525.4 KiB
+    "stress": {"kernel": "score_traj", "sha256": "789ae5d69b5a52c03ba2135215363a79375a4d6d2ae7d70541264fb32f592c18", "bytes": 203393228},
+    # profiles/filter_step_hbm_counters.md: FETCH_SIZE 103743.5 KiB, WRITE_SIZE 1140.4 KiB
+    "wide": {"kernel": "score_reduce", "sha256": "0833fb7d0a2cb8c1dab86efc176261f12a35f94261305165f25299beb844a346", "bytes": 213634457},
 }
 
 
@@ -294,7 +298,7 @@ def measure_pool(pace, pool, host_cols, mode, K, dev, stream, cus, config_name):
         "kernel_us_mean": kus,
         "roofline": {"kernel": dom, "bound": "hbm", "achieved": kb[dom] / t_dom / 1e9,
                      "peak": HBM_PEAK / 1e9, "unit": "GB/s", "frac": kb[dom] / t_dom / HBM_PEAK,
-                     "traffic": reduce_traffic(config_name, len(host_cols)) if dom == "score_reduce" else None,
+                     "traffic": score_traffic(dom, config_name, len(host_cols)),
                      "alg_bytes": kb[dom]},
         "timing": "%d steps back to back between one event pair over %d rotating pool copies, each copy "
                   "evicted from L2 and MALL before its turn; host enqueue %.2f ms of %.2f ms wall"
