@@ -183,7 +183,7 @@ SCORE_COUNTERS = {
     # profiles/filter_step_hbm_counters.md: FETCH_SIZE 99050.4 KiB, WRITE_SIZE 525.4 KiB
     "stress": {"kernel": "score_traj", "sha256": "789ae5d69b5a52c03ba2135215363a79375a4d6d2ae7d70541264fb32f592c18", "bytes": 203393228},
     # profiles/filter_step_hbm_counters.md: FETCH_SIZE 103743.5 KiB, WRITE_SIZE 1140.4 KiB
-    "wide": {"kernel": "score_reduce", "sha256": "0833fb7d0a2cb8c1dab86efc176261f12a35f94261305165f25299beb844a346", "bytes": 213634457},
+    "wide": {"kernel": "score_reduce", "sha256": "d60133e0ff808e8d698bc292ce271a5cae10580bb69fcd1460566173d77fa5a4", "bytes": 213634457},
 }
 
 

@@ -1,4 +1,6 @@
-// pace_score kernels for gfx950.
+// pace_score kernels for gfx950: scores over equal chunks of tokens, for pools
+// of many short trajectories (score_by_traj says which; the others are scored
+// by trajectory, score_traj.hip).
 //
 // Step 1 (score_reduce): every per-token version tag is read exactly once.
 // The token array is cut into equal chunks of consecutive tokens, one per
