@@ -198,6 +198,9 @@ constexpr int kPW = kPT / kWave;          // its waves
 constexpr int kCopyU = 4;                 // 16-byte loads in flight per thread in a range copy
 constexpr int64_t kRangeMin = 1024;       // tokens of a range when the batch does not fill the chip
 constexpr int64_t kRangeLen = 3584;       // tokens of a range when it does
+constexpr int64_t kRangeLeast = 2048;     // a range is no shorter than this or the pool's mean trajectory
+constexpr int64_t kRangePool = 16384;     // tokens of the pool per range, at most, whatever is expected to be kept
+constexpr int64_t kRangeSpans = 2;        // kept trajectories per range, at most, while the chip is not full
 constexpr int64_t kWaveCopy = 2048;       // a span part of at most this many bytes is one wave's
 
 // Span length of trajectory i if kept (offsets clamped to [0, NT]), else 0.
@@ -277,62 +280,131 @@ __device__ __forceinline__ void copy_part(const char *__restrict__ src, char *__
     else if ((turn++ & (kPW - 1)) == wv) copy_bytes<kWave>(src, dst, nb, lane_id());
 }
 
-// The block partials of at most kWave * kPL blocks, kPL consecutive ones per
-// lane, and their exclusive prefix at the lane's first.
-template <typename T, int kPL>
-struct LaneParts {
-    T v[kPL];
-    T before, total;
-    __device__ __forceinline__ void load(const T *__restrict__ x, int64_t nb) {
-        const int64_t b0 = (int64_t)lane_id() * kPL;
-        T sum = 0;
+// Inclusive sums of the block partials x[0 .. nb). kC > 0: kPW * kC * 64 blocks
+// at most, kC chunks of 64 per wave, summed once by the workgroup and kept in
+// LDS (a barrier); every wave loading all 512 partials of an 8192-trajectory
+// pool by itself took 3 to 8 us of a 10 us compaction. kC = 0: at most 64
+// blocks, in the registers of every wave; no barrier, 0.8 us of a
+// 1024-trajectory step.
+template <typename T, int kC>
+struct BlockSums {
+    static constexpr int kPer = (kC > 0 ? kC : 1) * kWave;      // blocks a wave sums
+    struct Smem {
+        T sum[kC > 0 ? kPW * kPer : 1];                         // inclusive, within the wave's blocks
+        T tot[kPW];
+    };
+    Smem &sm;
+    int64_t start[kPW];                                         // sum before wave w's blocks
+    int64_t all;
+    T reg;                                                      // kC = 0: the lane's inclusive sum
+    T v[kC > 0 ? kC : 1];
+    __device__ __forceinline__ explicit BlockSums(Smem &s) : sm(s) {}
+    __device__ __forceinline__ void load(const T *__restrict__ x, int64_t nb, int wv) {
 #pragma unroll
-        for (int k = 0; k < kPL; ++k) {
-            v[k] = b0 + k < nb ? x[b0 + k] : (T)0;
-            sum += v[k];
+        for (int c = 0; c < kPer / kWave; ++c) {
+            const int64_t b = (kC > 0 ? wv * kPer : 0) + c * kWave + lane_id();
+            v[c] = b < nb ? x[b] : (T)0;
         }
-        const int64_t incl = wave_incl_scan_i64((int64_t)sum);
-        before = (T)(incl - (int64_t)sum);
-        total = (T)readlane_i64(incl, kWave - 1);
     }
-    // Prefix before block b (wave-uniform b).
-    __device__ __forceinline__ int64_t prefix(int64_t b) const {
-        int64_t p = (int64_t)before;
+    // After load; with kC > 0 a barrier belongs between scan and finish.
+    __device__ __forceinline__ void scan(int wv) {
+        int64_t run = 0;
 #pragma unroll
-        for (int k = 0; k < kPL; ++k) p += k < (int)(b % kPL) ? (int64_t)v[k] : 0;
-        return readlane_i64(p, (int)(b / kPL));
+        for (int c = 0; c < kPer / kWave; ++c) {
+            const int64_t incl = run + wave_incl_scan_i64((int64_t)v[c]);
+            if constexpr (kC > 0) sm.sum[wv * kPer + c * kWave + lane_id()] = (T)incl;
+            else reg = (T)incl;
+            run = readlane_i64(incl, kWave - 1);
+        }
+        all = run;
+        if (kC > 0 && lane_id() == 0) sm.tot[wv] = (T)run;
+    }
+    __device__ __forceinline__ void finish() {
+        start[0] = 0;
+        if constexpr (kC > 0) {
+            all = 0;
+#pragma unroll
+            for (int w = 0; w < kPW; ++w) {
+                start[w] = all;
+                all += readlane_i64((int64_t)sm.tot[w], 0);
+            }
+        }
+    }
+    // Sum before block b, and the first block whose inclusive sum is above x
+    // (x below `all`), with the sums before it and through it: all wave-uniform.
+    __device__ __forceinline__ int64_t before(int64_t b) const {
+        if constexpr (kC == 0) {
+            const int64_t s = readlane_i64((int64_t)reg, b > 0 ? (int)b - 1 : 0);
+            return b > 0 ? s : 0;
+        }
+        int64_t s = b % kPer ? (int64_t)sm.sum[b - 1] : 0;
+#pragma unroll
+        for (int w = 1; w < kPW; ++w) s += b / kPer == w ? start[w] : 0;
+        return s;
+    }
+    __device__ __forceinline__ int64_t find(int64_t x, int64_t &lo, int64_t &hi) const {
+        int w = 0;
+        lo = 0;
+        if constexpr (kC > 0) {
+#pragma unroll
+            for (int k = 1; k < kPW; ++k) {
+                if (x >= start[k]) {
+                    w = k;
+                    lo = start[k];
+                }
+            }
+        }
+        const int64_t base = lo;
+        int64_t b = w * kPer;
+        hi = lo;
+#pragma unroll
+        for (int c = 0; c < kPer / kWave; ++c) {
+            const int64_t incl = base + (int64_t)(kC > 0 ? sm.sum[kC > 0 ? w * kPer + c * kWave + lane_id() : 0] : reg);
+            const uint64_t m = ballot(incl > x);
+            const int j = m ? __ffsll((long long)m) - 1 : kWave;
+            if (j > 0) lo = readlane_i64(incl, j - 1);
+            b += j;
+            if (m) {
+                hi = readlane_i64(incl, j);
+                break;
+            }
+        }
+        return b;
     }
 };
 
 // Workgroups [0, n_idx) write the index outputs (packed offsets, kept ids,
 // rejected ids), one block per wave. Then workgroup n_idx + r of grid row col
-// copies packed tokens [r S, (r + 1) S) of column col, S = ceil(total / n_rng):
-// bound by memory, so the output is cut evenly whatever the spans' lengths,
-// finely enough that workgroups ending early leave room for others, and by
-// column (the ranges of one column before the next's). Every wave looks its
-// range up by itself (the block partials in its lanes, a wave scan, then the
-// block's 16 spans): no barrier and no LDS, 56 VGPRs, so that eight
-// workgroups share a CU and one's look-up hides under the others' copies. All
-// waves copy a long span part together; parts of at most kWaveCopy bytes go to
-// the waves in turn. offsets_out, kept_ids and n_kept_tokens may be null
-// (rejected ids only).
+// copies packed tokens [r S, (r + 1) S) of column col, S = ceil(total / n_rng)
+// or `least`, the longer: bound by memory, so the output is cut evenly whatever
+// the spans' lengths, finely enough that workgroups ending early leave room for
+// others, and by column (the ranges of one column before the next's). Each
+// looks its range up in the block partials' sums, then in the block's 16 spans;
+// 60 to 64 VGPRs, so that eight workgroups share a CU and one's look-up hides
+// under the others' copies. All waves copy a long span part together; parts of
+// at most kWaveCopy bytes go to the waves in turn. offsets_out, kept_ids and
+// n_kept_tokens may be null (rejected ids only).
 // Against whole spans cut into pieces of 16,384 tokens with all columns in one
-// workgroup: 10M kept tokens in 3 columns 61 -> 45 us, 16.9M in 4 columns
-// 100 -> 80 us, 16.7M in one column 26 -> 25 us.
-template <int kPL>
+// workgroup, a fused step: 10M kept tokens in 3 columns 86 -> 67 us, 16.9M in 4
+// columns 149 -> 97 us, 16.7M in one column 79 -> 71 us.
+template <int kC>
 __global__ __launch_bounds__(kPT) void compact_range_kernel(
     const int64_t *__restrict__ off, int64_t n, int64_t NT, const uint8_t *__restrict__ keep,
-    PieceParts parts, int64_t nb, int64_t n_idx, int64_t n_rng, CompactCols cols, int n_cols,
+    PieceParts parts, int64_t nb, int64_t n_idx, int64_t n_rng, int64_t least, CompactCols cols,
     int64_t *__restrict__ offsets_out, int32_t *__restrict__ kept_ids, int64_t *__restrict__ n_kept_tokens,
     int32_t *__restrict__ reject_ids, int64_t budget) {
+    __shared__ typename BlockSums<int64_t, kC>::Smem s_len;
+    __shared__ typename BlockSums<int32_t, kC>::Smem s_cnt;
     const int lane = lane_id();
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const int64_t q = blockIdx.x;
-    LaneParts<int64_t, kPL> L;
+    BlockSums<int64_t, kC> L(s_len);
+    L.load(parts.len, nb, wv);
     if (q < n_idx) {
         if (blockIdx.y != 0) return;
+        BlockSums<int32_t, kC> C(s_cnt);
+        C.load(parts.cnt, nb, wv);
         const int64_t b = q * kPW + wv;
-        if (b >= nb && q != 0) return;
         const int64_t i = b * kPieceBlock + lane;
         const bool in = lane < kPieceBlock && i < n;
         int64_t len = 0, lo;
@@ -342,16 +414,18 @@ __global__ __launch_bounds__(kPT) void compact_range_kernel(
             kept = k >= 0;
             len = kept ? k : 0;
         }
-        LaneParts<int32_t, kPL> C;
-        L.load(parts.len, nb);
-        C.load(parts.cnt, nb);
+        L.scan(wv);
+        C.scan(wv);
+        if (kC > 0) __syncthreads();
+        L.finish();
+        C.finish();
         if (q == 0 && threadIdx.x == 0 && offsets_out) {
-            offsets_out[C.total] = L.total;
-            *n_kept_tokens = L.total;
+            offsets_out[C.all] = L.all;
+            *n_kept_tokens = L.all;
         }
         if (b >= nb) return;
-        const int64_t rank = C.prefix(b) + (int64_t)__popcll(ballot(kept) & lanes_below());
-        const int64_t dst = L.prefix(b) + (wave_incl_scan_i64(len) - len);
+        const int64_t rank = C.before(b) + (int64_t)__popcll(ballot(kept) & lanes_below());
+        const int64_t dst = L.before(b) + (wave_incl_scan_i64(len) - len);
         if (kept) {
             if (offsets_out) {
                 offsets_out[rank] = dst;
@@ -364,49 +438,33 @@ __global__ __launch_bounds__(kPT) void compact_range_kernel(
         return;
     }
 
-    // Copy: packed tokens [x0, x1).
-    const int64_t r = q - n_idx;
-    const int col = blockIdx.y;
-    L.load(parts.len, nb);
-    const int64_t total = L.total < NT ? L.total : NT;   // malformed offsets could overflow the output
+    // Copy: packed tokens [x, x1).
+    L.scan(wv);
+    if (kC > 0) __syncthreads();
+    L.finish();
+    const int64_t total = L.all < NT ? L.all : NT;   // malformed offsets could overflow the output
     int64_t S = (total + n_rng - 1) / n_rng;
-    S = (S + 63) / 64 * 64;
-    const int64_t x0 = r * S;
-    if (x0 >= total) return;
+    S = S > least ? S : least;
+    S = S < 512 ? (S + 15) / 16 * 16 : (S + 63) / 64 * 64;
+    int64_t x = (q - n_idx) * S;
+    if (x >= total) return;
+    const int64_t x0 = x;
     const int64_t x1 = x0 + S < total ? x0 + S : total;
-
+    const int col = blockIdx.y;
     const int64_t E = cols.elem[col];
     const char *in = (const char *)cols.in[col];
     char *out = (char *)cols.out[col];
-
-    // The block holding x0: the last with tokens whose prefix is at or before it.
-    int64_t b, lb;
-    {
-        int64_t p = L.before, mb = -1, mp = 0;
-#pragma unroll
-        for (int k = 0; k < kPL; ++k) {
-            if (L.v[k] > 0 && p <= x0) {
-                mb = (int64_t)lane * kPL + k;
-                mp = p;
-            }
-            p += L.v[k];
-        }
-        const uint64_t m = ballot(mb >= 0);
-        const int top = m ? 63 - __clzll((long long)m) : 0;
-        b = readlane_i64(mb, top);
-        lb = readlane_i64(mp, top);
-        if (m == 0) return;
-    }
     int turn = 0;
-    while (true) {
+    while (x < x1) {
+        int64_t lb, nx;
+        const int64_t b = L.find(x, lb, nx);
         const int64_t i = b * kPieceBlock + lane;
         int64_t len = 0, lo = 0;
         if (lane < kPieceBlock && i < n) {
             const int64_t k = kept_span(off, keep, i, NT, lo);
             len = k > 0 ? k : 0;
         }
-        const int64_t incl = wave_incl_scan_i64(len);
-        const int64_t d = lb + incl - len;
+        const int64_t d = lb + wave_incl_scan_i64(len) - len;
         uint64_t m = ballot(len > 0 && d < x1 && d + len > x0);
         while (m) {
             const int j = __ffsll((long long)m) - 1;
@@ -416,18 +474,8 @@ __global__ __launch_bounds__(kPT) void compact_range_kernel(
             const int64_t e = dj + lj < x1 ? dj + lj : x1;
             copy_part(in + (sj + (a - dj)) * E, out + a * E, (e - a) * E, wv, turn);
         }
-        lb += readlane_i64(incl, kWave - 1);
-        if (lb >= x1) return;
-        // The next block with kept tokens.
-        int64_t nx = INT64_MAX;
-#pragma unroll
-        for (int k = kPL - 1; k >= 0; --k) {
-            const int64_t c = (int64_t)lane * kPL + k;
-            if (L.v[k] > 0 && c > b) nx = c;
-        }
-        const uint64_t mm = ballot(nx != INT64_MAX);
-        if (!mm) return;
-        b = readlane_i64(nx, __ffsll((long long)mm) - 1);
+        if (nx <= x) return;
+        x = nx;
     }
 }
 
@@ -953,12 +1001,28 @@ static int64_t expected_kept(int64_t n, int64_t n_tokens, int64_t kept) {
 // 4870 trajectories of 620 tokens and four columns, 2040 workgroups take 2 us
 // less than 3500; at 10M kept tokens and three columns, 2436 to 3072 ranges of a
 // column take 2 us less than 683 and 3 us less than 4096.
+// The survivors need not be of mean length, and spans of a few tokens cost a
+// round trip each and not their bytes, so the expected tokens do not decide
+// alone. One range per kRangePool tokens of the pool: 4 survivors of 400,000
+// tokens among 8192 trajectories, a step of 143 us with the 5 ranges of the
+// expected tokens, 35 us with these. One range per kRangeSpans survivors: 300
+// trajectories of 20 tokens, 100 kept, 46 us with 1 range, 13 us with 50.
 static int64_t range_count(int64_t n, int64_t n_tokens, int n_cols, int64_t max_kept) {
     const int64_t cus = resident_waves() / 16;
-    const int64_t est = expected_kept(n, n_tokens, max_kept < 0 ? 0 : std::min(max_kept, n));
-    const int64_t fill = std::min(est / kRangeMin, cus * 8 / n_cols);
+    const int64_t kept = max_kept < 0 ? 0 : std::min(max_kept, n);
+    const int64_t est = expected_kept(n, n_tokens, kept);
+    const int64_t want = std::max({est / kRangeMin, n_tokens / kRangePool, kept / kRangeSpans});
+    const int64_t fill = std::min(want, cus * 8 / n_cols);
     const int64_t fine = std::min(est / kRangeLen, cus * 12);
     return std::max<int64_t>(std::max(fill, fine), 1);
+}
+
+// Least tokens of a range, where fewer are kept than the count above allows for
+// (pace_compact cannot know): a range is a look-up, so it holds a mean
+// trajectory or kRangeLeast tokens. 819 of 8192 trajectories of 2000 tokens kept,
+// one column: 15.1 us in 3072 ranges, 9.5 in 820.
+static int64_t range_least(int64_t n, int64_t n_tokens) {
+    return n > 0 ? std::min(kRangeLeast, n_tokens / n) : kRangeLeast;
 }
 
 bool small_step_ok(int64_t n, int64_t n_tokens, int n_cols, int64_t budget) {
@@ -971,7 +1035,10 @@ hipError_t launch_rank_compact_small(const double *score, const int64_t *offsets
                                      int64_t *offsets_out, int32_t *kept_ids, int64_t *n_kept_tokens,
                                      int32_t *reject_ids, hipStream_t stream, const ScoreJoin &join) {
     if (n > kSmallMaxN) return hipErrorInvalidValue;
-    const int64_t n_rng = n_cols > 0 ? std::max<int64_t>(expected_kept(n, n_tokens, n - budget) / kRangeMin, 1) : 1;
+    // As many ranges as range_count has for such batches (few columns and tokens
+    // by small_step_ok): 200 trajectories of 20 tokens, 66 kept, 33 us a step
+    // with the one range of the expected tokens, 13.5 with 33.
+    const int64_t n_rng = n_cols > 0 ? range_count(n, n_tokens, n_cols, n - budget) : 1;
     const dim3 grid((unsigned)n_rng, (unsigned)(n_cols > 0 ? n_cols : 1));
     if (join.cap)
         return launch(kPhaseCompact, rank_compact_small_kernel<true>, grid, dim3(kPT), stream,
@@ -993,12 +1060,12 @@ hipError_t launch_compact_pieces(const int64_t *offsets, int64_t n, int64_t n_to
         const int64_t n_rng = copy && n_cols > 0 ? range_count(n, n_tokens, n_cols, max_kept) : 0;
         const dim3 grid((unsigned)(n_idx + n_rng), (unsigned)(copy && n_cols > 0 ? n_cols : 1));
 #define PACE_RANGES(P)                                                                                          \
-    return launch(kPhaseCompact, compact_range_kernel<P>, grid, dim3(kPT), stream, offsets, n,    \
-                  n_tokens, keep, parts, nb, n_idx, n_rng, cols, copy ? n_cols : 0, offsets_out, kept_ids,        \
-                  n_kept_tokens, reject_ids, budget)
-        if (nb <= kWave) PACE_RANGES(1);
-        if (nb <= 4 * kWave) PACE_RANGES(4);
-        PACE_RANGES(8);
+    return launch(kPhaseCompact, compact_range_kernel<P>, grid, dim3(kPT), stream, offsets, n, n_tokens, keep,  \
+                  parts, nb, n_idx, n_rng, range_least(n, n_tokens), cols, offsets_out, kept_ids, n_kept_tokens, \
+                  reject_ids, budget)
+        if (nb <= kWave) PACE_RANGES(0);
+        if (nb <= 4 * kWave) PACE_RANGES(1);
+        PACE_RANGES(2);
 #undef PACE_RANGES
     }
     if (blk != kWideBlock || (nb + kGroupBlocks - 1) / kGroupBlocks > kWideMaxGroups) return hipErrorInvalidValue;
