@@ -102,7 +102,10 @@ __device__ __forceinline__ uint32_t packed(int x) {
 // Four tags, dword-aligned: one load wherever the column starts. (Element loads
 // for tags off 16-byte alignment: 17M tags in 20,417 trajectories, a score call
 // 6 us longer.) The launch bound keeps kReduceWavesPerCU waves resident in every
-// arithmetic; without it the 32- and 64-bit ones took 130 to 133 VGPRs, twelve.
+// arithmetic; without it the 64-bit one takes 133 VGPRs, twelve waves. With it
+// that one spills 24 bytes a lane and is the faster all the same; a score call
+// without / with the bound, V = 2^30: 65,536 trajectories, 45.9M tokens 56.1 /
+// 50.4 us; 20,000, 16M 25.3 / 23.8; 8300, 8.3M 16.5 / 16.8.
 __device__ __forceinline__ int4 load_tags(const int32_t *p) {
     const uint4 x = load_a4(p);
     return make_int4((int)x.x, (int)x.y, (int)x.z, (int)x.w);
