@@ -119,3 +119,76 @@ def test_malformed_offsets_give_the_walks_flags(pace):
         sys.stdout.write("[gpu] validate malformed %d want %d\n" % (k, want))
         sys.stdout.flush()
         assert _run(pace, tags, bad, comp) == want
+
+
+def _short(kind, rng):
+    """Trajectories that a wave takes one per lane, and their neighbours: over 128
+    tokens on average, over 1024 at most, batches cut by a chunk's end, by the
+    last trajectory and by empty ones, and fewer than four tokens in all."""
+    L = {"mean": rng.integers(100, 157, 400), "most": np.r_[rng.integers(0, 40, 70), 1024, rng.integers(0, 40, 90), 1025,
+                                                          rng.integers(0, 40, 333)],
+         "empty": np.where(rng.random(2000) < 0.9, 0, rng.integers(1, 300, 2000)),
+         "steps": np.tile([15, 16, 17, 1, 31, 32, 33, 0], 90), "few": np.array([1, 0, 2]), "four": np.array([0, 1, 3])}[kind]
+    off = np.concatenate([[0], np.cumsum(L)]).astype(np.int64)
+    comp = rng.integers(0, V + 1, len(L)).astype(np.int32)
+    tags = np.repeat(comp, L).astype(np.int32)
+    tags[rng.random(len(tags)) < 0.2] = -1
+    return off, comp, tags
+
+
+@pytest.mark.parametrize("kind", ["mean", "most", "empty", "steps", "few", "four"])
+def test_bad_tag_in_short_trajectories(pace, kind):
+    rng = np.random.default_rng(7)
+    off, comp, tags = _short(kind, rng)
+    N, n = len(tags), len(comp)
+    traj = np.repeat(np.arange(n), np.diff(off))
+    at = {0, 1, 2, N - 1, N - 2, N - 3, N - 4, N - 5} | {p + d for p in range(8192, N, 8192) for d in (-2, -1, 0, 1)}
+    at |= {int(p) + d for p in rng.choice(off, 40) for d in (-2, -1, 0, 1)}
+    for lead in (0, 1):
+        sys.stdout.write("[gpu] validate short %s lead %d tokens %d\n" % (kind, lead, N))
+        sys.stdout.flush()
+        assert _run(pace, tags, off, comp, lead) == 0
+        for p in sorted(p for p in at if 0 <= p < N):
+            for bad in (int(comp[traj[p]]) + 1, -2):
+                t = tags.copy()
+                t[p] = bad
+                assert _run(pace, t, off, comp, lead) == pace.BAD_TAG, (p, bad)
+
+
+@pytest.mark.parametrize("kind", ["mean", "most", "empty", "steps"])
+def test_malformed_short_trajectories_give_the_walks_flags(pace, kind):
+    rng = np.random.default_rng(13)
+    off, comp, tags = _short(kind, rng)
+    for k in range(12):
+        bad = off.copy()
+        j = rng.integers(0, len(off), 1 + k % 4)
+        bad[j] = bad[j] + rng.integers(-300, 300, len(j)) if k % 2 else rng.integers(-5, len(tags) + 5, len(j))
+        want = pace.BAD_TAG if _walk(tags, bad, comp) else 0
+        mono = (np.diff(bad) >= 0).all() and bad[0] == 0 and bad[-1] == len(tags)
+        want |= 0 if mono else pace.BAD_OFFSETS
+        sys.stdout.write("[gpu] validate malformed short %s %d want %d\n" % (kind, k, want))
+        sys.stdout.flush()
+        assert _run(pace, tags, bad, comp) == want
+
+
+def test_short_trajectories_do_not_cost_a_round_trip_each(pace):
+    """200,000 trajectories of 20 tokens: 245 us a call with the trajectories of
+    a chunk one after the other, 18 with one per lane; calls back to back, the
+    best of five rounds."""
+    n, L = 200000, 20
+    off = torch.arange(0, n * L + 1, L, dtype=torch.int64, device="cuda:0")
+    tags = torch.full((n * L,), 3, dtype=torch.int32, device="cuda:0")
+    comp = torch.full((n,), 5, dtype=torch.int32, device="cuda:0")
+    err = torch.zeros(1, dtype=torch.int32, device="cuda:0")
+    us = []
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        pace.pace_validate(tags, off, comp, V, err_out=err)
+        a.record()
+        for _ in range(20):
+            pace.pace_validate(tags, off, comp, V, err_out=err)
+        b.record()
+        torch.cuda.synchronize()
+        us.append(a.elapsed_time(b) * 1e3 / 20)
+    sys.stdout.write("[gpu] validate 200,000 trajectories of 20 tokens: %.1f us\n" % min(us))
+    assert int(H(err)[0]) == 0 and min(us) < 120
