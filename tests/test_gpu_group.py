@@ -206,3 +206,43 @@ def test_validate_groups(pace):
         say("validate groups %s n=%d" % (go, n))
         e = int(H(pace.pace_validate_groups(D(np.array(go, np.int64)), n))[0])
         assert (e == pace.BAD_GROUPS) == bad and e in (0, pace.BAD_GROUPS)
+
+
+@pytest.mark.parametrize("ng", [1, 2, 40, 300])
+def test_long_groups(pace, ng):
+    """Groups whose members are loaded sixteen at a time, with every remainder,
+    some members summed in pieces (over 16,384 tokens here) among them."""
+    rng = np.random.default_rng(ng)
+    n = 5000
+    L = rng.integers(0, 60, n)
+    L[[0, 15, 16, 17, 700, n - 1]] = [16385, 40000, 16384, 70001, 33000, 20000]
+    pool = poolgen.make_custom_pool(L, V=90, seed=ng)
+    cut = np.sort(rng.integers(0, n + 1, ng - 1))
+    cut[: min(20, ng - 1)] = np.arange(1, 21)[: min(20, ng - 1)] * 17
+    go = np.concatenate([[0], np.sort(cut), [n]]).astype(np.int64)
+    say("long groups ng=%d sizes %s" % (ng, np.diff(go)[:8]))
+    group_step_parity(pace, pool, go, ng, max(1, ng // 2))
+
+
+def test_a_long_group_costs_no_round_trip_per_eight_members(pace):
+    """Group step of 8192 trajectories of 500 tokens in two groups, where some
+    trajectory could be summed in pieces: the rank over groups takes 216 us with
+    its members eight at a time, every batch searched for pieces, and 95 as it
+    is. The best of ten."""
+    n = 8192
+    off = torch.arange(0, n * 500 + 1, 500, dtype=torch.int64, device=DEV)
+    tags = torch.full((n * 500,), 3, dtype=torch.int32, device=DEV)
+    comp = torch.full((n,), 5, dtype=torch.int32, device=DEV)
+    go = torch.tensor([0, n // 2, n], dtype=torch.int64, device=DEV)
+    best = float("inf")
+    for _ in range(10):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        b.record()
+        torch.cuda.synchronize()
+        pace.pace_time_next_kernel(pace.PHASE_SELECT, a, b)
+        pace.pace_group_filter_step(tags, off, comp, 7, go, 2, 1, [tags])
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3)
+    say("rank over two groups of 4096: %.1f us" % best)
+    assert best < 140
