@@ -13,8 +13,8 @@ namespace pace {
 namespace {
 
 constexpr int64_t kValChunk = 8192;   // tokens per wave
-constexpr int64_t kLaneMean = 128;    // trajectories of at most this many tokens on average, and
-constexpr int64_t kLaneMost = 1024;   // at most that many each: one per lane
+constexpr int64_t kLaneMean = 128;    // trajectories of at most this many tokens on average: one per lane
+constexpr int64_t kLaneStep = 16;     // tokens per lane and round trip
 
 __global__ void validate_init_kernel(int32_t *err) { *err = 0; }
 
@@ -58,10 +58,15 @@ __device__ __forceinline__ uint32_t max_tag1(const int32_t *__restrict__ tags, i
 // order, from lo on, limits lim), four vectors per lane in flight. False, with
 // nothing done, when they are not short or the ends are not in order; else lo
 // moves to the last end. Taken one after the other each trajectory costs the
-// wave a round trip, one per lane a batch costs one per 16 tokens of its longest
-// but reads whole lines for its vectors: 400,000 trajectories of 5 tokens 793 ->
-// 53 us, 65,536 of 64 88 -> 21, of 120 52 -> 41 (28 if all batches took it); of
-// 200 it would be 36 -> 44.
+// wave a round trip, one per lane a batch costs one per kLaneStep tokens of its
+// longest but reads whole lines for its vectors; so one per lane where that is
+// no more round trips and kLaneMean holds. One after the other / one per lane:
+// 400,000 trajectories of 5 tokens 721 / 36 us, 65,536 of 64 80 / 11, of 120 48
+// / 16, of 200 36 / 44 (that is why kLaneMean); 262,144 log-normal lengths of
+// 100 on average 84 / 85. A lane with no more tokens reads the vector that all
+// such lanes read: reading on along its own, those 262,144 took 201 us. (Loads
+// behind a branch instead, or a loop that lanes leave one by one, slow the other
+// walk of the kernel down: 100,000 of 200 tokens 36 -> 42 us.)
 __device__ __forceinline__ bool lane_segments(const int32_t *__restrict__ tags, int64_t NT, bool active, int64_t h,
                                               uint32_t lim, int64_t ce, int64_t &lo, int64_t front, bool &bad) {
     const uint64_t act = ballot(active);
@@ -73,13 +78,17 @@ __device__ __forceinline__ bool lane_segments(const int32_t *__restrict__ tags, 
                                     (uint32_t)__builtin_amdgcn_ds_bpermute(up, (int)(uint32_t)h));
     const int64_t a = lane_id() == first ? lo : below, e = h < ce ? h : ce;
     const int64_t len = active && e > a ? e - a : 0;
-    if (ballot(active && (h < a || len > kLaneMost)) || tokens > kLaneMean * __popcll(ballot(len > 0))) return false;
-    for (int64_t p = a; ballot(p - a < len); p += 16) {
+    const int64_t some = __popcll(ballot(len > 0));
+    if (tokens > kLaneMean * some || ballot(active && (h < a || len > kLaneStep * some))) return false;
+    for (int64_t p = a; ballot(p - a < len); p += kLaneStep) {
         uint4 x[4];
         int64_t q[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            q[u] = p + 4 * u < NT - 4 ? p + 4 * u : NT - 4;      // in the array; tokens outside [a, e) are dropped
+            // In the array; tokens outside [a, e) are dropped. Where a lane has
+            // no more, it reads the vector that all such lanes read.
+            q[u] = p + 4 * u - a < len ? p + 4 * u : lo;
+            q[u] = q[u] < NT - 4 ? q[u] : NT - 4;
             x[u] = load_a4(tags + q[u]);
         }
         uint32_t m = 0;

@@ -123,10 +123,13 @@ def test_malformed_offsets_give_the_walks_flags(pace):
 
 def _short(kind, rng):
     """Trajectories that a wave takes one per lane, and their neighbours: over 128
-    tokens on average, over 1024 at most, batches cut by a chunk's end, by the
-    last trajectory and by empty ones, and fewer than four tokens in all."""
+    tokens on average, a lane's share of 16 tokens per trajectory of the batch
+    and one more (64 and 9 of them), batches cut by a chunk's end, by the last
+    trajectory and by empty ones, and fewer than four tokens in all."""
     L = {"mean": rng.integers(100, 157, 400), "most": np.r_[rng.integers(0, 40, 70), 1024, rng.integers(0, 40, 90), 1025,
                                                           rng.integers(0, 40, 333)],
+         "share": np.r_[np.full(63, 3), 1024, np.full(63, 3), 1025, np.full(63, 3), 1009, np.full(8, 3), 144],
+         "share9": np.r_[np.full(4, 3), 145, np.full(4, 3)],
          "empty": np.where(rng.random(2000) < 0.9, 0, rng.integers(1, 300, 2000)),
          "steps": np.tile([15, 16, 17, 1, 31, 32, 33, 0], 90), "few": np.array([1, 0, 2]), "four": np.array([0, 1, 3])}[kind]
     off = np.concatenate([[0], np.cumsum(L)]).astype(np.int64)
@@ -136,7 +139,7 @@ def _short(kind, rng):
     return off, comp, tags
 
 
-@pytest.mark.parametrize("kind", ["mean", "most", "empty", "steps", "few", "four"])
+@pytest.mark.parametrize("kind", ["mean", "most", "share", "share9", "empty", "steps", "few", "four"])
 def test_bad_tag_in_short_trajectories(pace, kind):
     rng = np.random.default_rng(7)
     off, comp, tags = _short(kind, rng)
@@ -155,7 +158,7 @@ def test_bad_tag_in_short_trajectories(pace, kind):
                 assert _run(pace, t, off, comp, lead) == pace.BAD_TAG, (p, bad)
 
 
-@pytest.mark.parametrize("kind", ["mean", "most", "empty", "steps"])
+@pytest.mark.parametrize("kind", ["mean", "most", "share", "empty", "steps"])
 def test_malformed_short_trajectories_give_the_walks_flags(pace, kind):
     rng = np.random.default_rng(13)
     off, comp, tags = _short(kind, rng)
@@ -171,14 +174,13 @@ def test_malformed_short_trajectories_give_the_walks_flags(pace, kind):
         assert _run(pace, tags, bad, comp) == want
 
 
-def test_short_trajectories_do_not_cost_a_round_trip_each(pace):
-    """200,000 trajectories of 20 tokens: 245 us a call with the trajectories of
-    a chunk one after the other, 18 with one per lane; calls back to back, the
-    best of five rounds."""
-    n, L = 200000, 20
-    off = torch.arange(0, n * L + 1, L, dtype=torch.int64, device="cuda:0")
-    tags = torch.full((n * L,), 3, dtype=torch.int32, device="cuda:0")
-    comp = torch.full((n,), 5, dtype=torch.int32, device="cuda:0")
+def _call_us(pace, lengths):
+    """A call on trajectories of these lengths: calls back to back, the best of
+    five rounds."""
+    off = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    tags = torch.full((int(off[-1]),), 3, dtype=torch.int32, device="cuda:0")
+    comp = torch.full((len(lengths),), 5, dtype=torch.int32, device="cuda:0")
+    off = D(off)
     err = torch.zeros(1, dtype=torch.int32, device="cuda:0")
     us = []
     for _ in range(5):
@@ -190,5 +192,28 @@ def test_short_trajectories_do_not_cost_a_round_trip_each(pace):
         b.record()
         torch.cuda.synchronize()
         us.append(a.elapsed_time(b) * 1e3 / 20)
-    sys.stdout.write("[gpu] validate 200,000 trajectories of 20 tokens: %.1f us\n" % min(us))
-    assert int(H(err)[0]) == 0 and min(us) < 120
+    assert int(H(err)[0]) == 0
+    return min(us)
+
+
+def test_short_trajectories_do_not_cost_a_round_trip_each(pace):
+    """200,000 trajectories of 20 tokens: 245 us a call with the trajectories of
+    a chunk one after the other, 18 with one per lane."""
+    us = _call_us(pace, np.full(200000, 20))
+    sys.stdout.write("[gpu] validate 200,000 trajectories of 20 tokens: %.1f us\n" % us)
+    assert us < 120
+
+
+@pytest.mark.parametrize("kind,limit", [("one long", 17.0), ("log-normal", 140.0)])
+def test_long_among_short_trajectories_do_not_hold_up_the_lanes(pace, kind, limit):
+    """15 trajectories of 5 tokens and one of 1000, and 262,144 of 100 on average
+    whose lengths vary: 25 and 201 us a call with one per lane wherever none is
+    above 1024 tokens (a lane with 1000 takes 63 round trips, and the others read
+    along), 10 and 85 as it is, 10 and 84 one after the other."""
+    L = np.r_[np.full(8, 5), 1000, np.full(7, 5)]
+    if kind == "log-normal":
+        w = np.exp(np.random.default_rng(1).standard_normal(262144))
+        L = (w / w.sum() * len(w) * 100).astype(np.int64)
+    us = _call_us(pace, L)
+    sys.stdout.write("[gpu] validate %s: %.1f us\n" % (kind, us))
+    assert us < limit
