@@ -304,12 +304,14 @@ __global__ __launch_bounds__(kDT) void diagnostics_slice_kernel(
 }
 
 // The one-launch form grows with the pool and with the search, the slices cost
-// a second launch. Calls back to back, one launch against slices: 64 bins, 8192
-// trajectories 7.2 / 9.7 us, 12,288 8.7 / 9.7, 16,384 11.0 / 9.7, 65,536 38.3 /
-// 9.7; 1000 bins, 4096 trajectories 7.7 / 10.3, 6000 10.7 / 10.4, 8192 12.5 /
-// 10.5.
-constexpr int64_t kDiagOneLaunchMax = 12288;
-inline bool diag_one_launch(int64_t n, int nbins) { return n * (nbins > 256 ? 2 : 1) <= kDiagOneLaunchMax; }
+// a second launch. Calls back to back, one launch against slices: 16 bins, 12,289
+// trajectories 10.8 / 12.5 us, 16,384 12.2 / 12.4; 64 bins, 14,336
+// 12.3 / 12.6, 16,384 13.1 / 12.5; 128 bins, 13,312 12.7 / 12.5; 256 bins, 12,288
+// 12.1 / 12.5; 1000 bins, 4096 7.7 / 10.3, 6000 10.7 / 10.4. (12,289 trajectories and 1 or 16 bins took 0.9 us more than before the
+// slices while the line was 12,288 for all up to 256 bins.)
+inline bool diag_one_launch(int64_t n, int nbins) {
+    return n <= (nbins > 256 ? 6144 : (nbins > 64 ? 12288 : (nbins > 32 ? 14336 : 16384)));
+}
 constexpr int64_t kDiagSlicesMax = 128;
 
 }  // namespace

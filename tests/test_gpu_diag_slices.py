@@ -20,6 +20,7 @@ def pace():
 
 
 @pytest.mark.parametrize("n,nb", [(6144, 257), (6145, 257), (6145, 1024), (12288, 256), (12289, 1), (12289, 256),
+                                  (12289, 65), (14336, 64), (14337, 33), (14337, 64), (16384, 32), (16385, 1), (16385, 32),
                                   (65536, 64), (131072 + 1025, 63)])
 def test_diagnostics_slices(pace, n, nb):
     rng = np.random.default_rng(n + nb)
