@@ -1012,10 +1012,6 @@ hipError_t launch_compact_partials(const int64_t *offsets, int64_t n, int64_t n_
                   offsets, n, n_tokens, keep, parts);
 }
 
-static int64_t expected_kept(int64_t n, int64_t n_tokens, int64_t kept) {
-    return n > 0 ? (int64_t)((double)n_tokens * ((double)kept / (double)n)) : 0;
-}
-
 // Ranges per column. max_kept / n of the tokens is the expected batch: as many
 // ranges as fill the chip once (8 workgroups per CU over all columns) while they
 // hold kRangeMin tokens, up to 12 per CU and column while they hold kRangeLen.
@@ -1045,11 +1041,6 @@ static int64_t range_count(int64_t n, int64_t n_tokens, int n_cols, int64_t max_
 // one column: 15.1 us in 3072 ranges, 9.5 in 820.
 static int64_t range_least(int64_t n, int64_t n_tokens) {
     return n > 0 ? std::min(kRangeLeast, n_tokens / n) : kRangeLeast;
-}
-
-bool small_step_ok(int64_t n, int64_t n_tokens, int n_cols, int64_t budget) {
-    const int64_t most = kSmallMaxCopy * (n <= kSmallMaxN / 2 ? 2 : 1) / (n_cols > 0 ? n_cols : 1);
-    return n <= kSmallMaxN && expected_kept(n, n_tokens, n - budget) <= most;
 }
 
 hipError_t launch_rank_compact_small(const double *score, const int64_t *offsets, int64_t n, int64_t n_tokens,

@@ -256,7 +256,7 @@ hipError_t launch_group_filter_step(const int32_t *tags, const int64_t *offsets,
         // members' flags, the compaction's partials (blocks of 16, or of 64
         // with group sums for the merge-path compaction) and the rejected ids.
         const CompactWs cw = compact_ws_carve(cws, N, n_tokens);
-        if ((ng + kRankQ - 1) / kRankQ * n <= kGroupRankLoads) {
+        if (group_means_in_rank(n, ng)) {
             e = launch_group_rank(score, n, group_offsets, ng, budget, group_score, group_keep, stream, join);
         } else {
             // Every rank workgroup re-forming every mean would read the

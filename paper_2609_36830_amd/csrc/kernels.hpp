@@ -9,6 +9,8 @@
 
 #include <tuple>
 
+#include "rules.hpp"
+
 namespace pace {
 
 // Waves the device keeps resident for the streaming kernels (CUs x 16).
@@ -115,10 +117,6 @@ hipError_t launch_score_finalize(const int64_t *offsets, int64_t n, int64_t n_to
                                  int64_t *gen_count, const ScoreWorkspace &ws, hipStream_t stream,
                                  uint64_t *mmin = nullptr, uint64_t *mmax = nullptr,
                                  uint32_t *hist0 = nullptr);
-// Whether the score is formed by trajectory (score_traj.hip) rather than over
-// equal chunks of tokens, and the most tokens that one workgroup then sums.
-bool score_by_traj(int64_t n, int64_t n_tokens);
-int64_t score_traj_cap(int64_t n, int64_t n_tokens);
 // Scores, S and T of every trajectory of at most score_traj_cap tokens, and
 // ws.traj; longer ones are left for the joining kernel or reader.
 hipError_t launch_score_traj(const int32_t *tags, const ScoreArgs &a, const ScoreWorkspace &ws, hipStream_t stream);
@@ -138,9 +136,6 @@ hipError_t launch_score(const int32_t *tags, const ScoreArgs &a, const ScoreWork
 // ---- select ----------------------------------------------------------------
 constexpr int kSelectThreads = 1024;
 constexpr int kSelectMaxItems = 16;   // keys held in registers per thread
-// Pools up to this size are selected by the multi-workgroup rank-by-counting
-// kernel; larger pools by the single-workgroup radix select.
-constexpr int64_t kRankMaxN = 8192;
 // ---- compaction by ranges: block partials -----------------------------------
 // Consecutive trajectories form blocks of kPieceBlock. Per block: kept count
 // and kept tokens (lengths from offsets clamped to [0, n_tokens]).
@@ -194,11 +189,7 @@ hipError_t launch_wide_cut(const double *score, int64_t n, int64_t budget, const
 // trajectories that were summed in pieces: their scores, S and T.
 // Group means of pace_group_score formed inside the rank over groups (at
 // most kRankMaxN groups): group scores and group keep flags in one launch.
-// Every rank workgroup (one per kRankQ groups) reads all member scores, so
-// the group step uses it while ceil(ng / kRankQ) * n stays within
-// kGroupRankLoads, and a separate pass of group means before the rank beyond.
-constexpr int kRankQ = 16;              // targets per rank workgroup
-constexpr int64_t kGroupRankLoads = (int64_t)1 << 21;
+// The group step uses it where group_means_in_rank.
 hipError_t launch_group_rank(const double *score, int64_t n, const int64_t *group_offsets, int64_t ng,
                              int64_t budget, double *group_score, uint8_t *group_keep, hipStream_t stream,
                              const ScoreJoin &join);
@@ -263,14 +254,6 @@ hipError_t launch_compact_pieces(const int64_t *offsets, int64_t n, int64_t n_to
                                  hipStream_t stream, int blk = kPieceBlock, bool copy = true);
 // Selection and compaction of the filter step in one launch, where
 // small_step_ok (scores as launch_rank takes them; n = 0 included).
-// Every workgroup repeats the ranking, so it is for batches that a few hundred
-// workgroups copy: expected kept tokens times columns up to kSmallMaxCopy, twice
-// that for at most half as many trajectories. Three launches / two, us a step:
-// 64 trajectories, 70K tokens 16.4 / 13.4; 64, 1.5M 16.0 / 14.3; 256, 1M 16.1 /
-// 14.1; 256, 2M 16.0 / 18.2; 256, 1M in three columns 17.0 / 21.3.
-constexpr int64_t kSmallMaxN = 256;
-constexpr int64_t kSmallMaxCopy = (int64_t)1 << 19;
-bool small_step_ok(int64_t n, int64_t n_tokens, int n_cols, int64_t budget);
 hipError_t launch_rank_compact_small(const double *score, const int64_t *offsets, int64_t n, int64_t n_tokens,
                                      int64_t budget, uint8_t *keep, const CompactCols &cols, int n_cols,
                                      int64_t *offsets_out, int32_t *kept_ids, int64_t *n_kept_tokens,

@@ -47,15 +47,14 @@ constexpr int kSub = 4;                       // windows per block of the fast p
 constexpr int kWavesPerBlock = 4;
 static_assert(kScoreChunkAlign % kWin == 0, "a chunk is whole windows");
 
-// Arithmetic of the reduction, chosen from V (tags are at most V):
+// Arithmetic of the reduction, chosen from V (reduce_mode):
 //   kPacked  every tag + 1 < 2^15: an element is q = (tag + 1) * 2^9 +
 //            [tag != -1], so that a window's 256 elements sum below 2^32 with
 //            the count in the low 9 bits; one 32-bit scan gives both prefixes,
 //            and a lane's running sums are kept as sum * 2^24 + count in 64
 //            bits (one wave reduction for both);
 //   kNarrow  every tag + 1 < 2^24: 32-bit window sums, counts separate;
-//   kWide    64-bit sums.
-enum ReduceMode : int { kPacked = 0, kNarrow = 1, kWideTags = 2 };
+//   kWideTags  64-bit sums.
 
 // Window-local exclusive prefixes of one window per wave, for the trajectory
 // boundaries inside it: sums (with the packed count), and for the other modes
@@ -491,8 +490,7 @@ hipError_t launch_score_reduce(const int32_t *tags, const int64_t *offsets, int6
     const int64_t ch = n_tokens > 0 ? (n_tokens + chunk_len - 1) / chunk_len : 0;
     if (n == 0 || ch == 0) return hipSuccess;
     const unsigned grid = (unsigned)((ch + kWavesPerBlock - 1) / kWavesPerBlock);
-    // Tags are at most V (a precondition): tag + 1 <= V + 1.
-    const int mode = (int64_t)V < (1 << 15) - 1 ? kPacked : ((int64_t)V < (1 << 24) - 1 ? kNarrow : kWideTags);
+    const ReduceMode mode = reduce_mode(V);
 #define PACE_REDUCE(MODE)                                                                \
     return launch(kPhaseReduce, score_reduce_kernel<MODE>, dim3(grid), dim3(256), stream,    \
                   tags, offsets, n, n_tokens, chunk_len, ch, ws.part_sum, ws.part_cnt,         \

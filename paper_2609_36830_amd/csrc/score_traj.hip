@@ -33,9 +33,6 @@ namespace pace {
 namespace {
 
 constexpr int kTU = 8;                             // 16-byte loads in flight per thread
-constexpr int64_t kTrajCap = 65536;                // tokens one workgroup of four or eight waves sums, at least
-constexpr int64_t kTrajOverMax = 4096;             // piece workgroups, at most (the cap grows instead)
-constexpr int64_t kTrajFillWaves = 4096;           // waves that few trajectories are spread over
 
 // Sums of one thread: the tags + 1 and the generated tokens.
 struct Narrow {                                    // a thread's tags, each at most V + 1, sum below 2^32
@@ -244,47 +241,14 @@ __global__ __launch_bounds__(kFinGroup) void score_join_kernel(ScoreJoin j, uint
 
 }  // namespace
 
-namespace {
-
-// Waves that take a trajectory, from the mean length: enough bytes for each
-// that its start and end (about 3 us) hide under the others' streams, and
-// enough waves for the chip when there are few trajectories. Whole steps, 1 / 2
-// / 4 / 8 waves: 8192 trajectories of 1464 tokens 38.9 / 39.4 / 41.4 / 53.0 us,
-// of 1953 42.0 / 42.2 / 43.4 / 54.5, 8000 of 3500 54.3 / 54.0 / 53.8 / 63.0,
-// 4096 of 6103 42.0 / 41.0 / 39.4 / 41.4, of 12,207 75.7 / 75.0 / 70.6 / 67.1.
-int traj_waves(int64_t n, int64_t n_tokens) {
-    const int64_t mean = n_tokens / n;
-    const int want = mean >= 8192 ? 8 : (mean >= 2560 ? 4 : (mean >= 1536 ? 2 : 1));
-    int fill = 1;
-    while (fill < 8 && fill * 2 * n <= kTrajFillWaves) fill *= 2;
-    return want > fill ? want : fill;
-}
-
-}  // namespace
-
-// Chunks of equal length remain for many short trajectories, where a
-// trajectory does not fill a wave's loads: 16,384 trajectories of 2500 tokens
-// take 75 us a step by chunks and 78 by trajectory, of 3200 90.4 and 89.2, 8200
-// of 5000 69 and 65.
-bool score_by_traj(int64_t n, int64_t n_tokens) { return n <= kRankMaxN || n_tokens / n >= 3072; }
-
-int64_t score_traj_cap(int64_t n, int64_t n_tokens) {
-    if (n == 0) return kTrajCap;
-    const int kw = traj_waves(n, n_tokens);
-    const int64_t least = kw >= 4 ? kTrajCap : kTrajCap / 4 * kw;
-    const int64_t per = n_tokens / kTrajOverMax;
-    return per <= least ? least : (per + least - 1) / least * least;
-}
-
 hipError_t launch_score_traj(const int32_t *tags, const ScoreArgs &a, const ScoreWorkspace &ws, hipStream_t stream) {
     if (a.n == 0) return hipSuccess;
     const int kw = traj_waves(a.n, a.NT);
     const int64_t cap = score_traj_cap(a.n, a.NT);
     const int64_t over = a.NT > cap ? (a.NT + cap - 1) / cap : 0;
     const dim3 grid((unsigned)(a.n + over));
-    // Tags are at most V (a precondition), so tag + 1 <= V + 1, and a thread
-    // sums at most cap / (64 kw) of them.
-    const bool narrow = (int64_t)a.V + 1 <= ((((int64_t)1 << 32) - 1) / (cap / (kWave * kw)));
+    static_assert(kWave == 64, "score_traj_narrow");
+    const bool narrow = score_traj_narrow(a.n, a.NT, a.V);
 #define PACE_TRAJ(W)                                                                                              \
     do {                                                                                                          \
         if (narrow) return launch(kPhaseReduce, score_traj_kernel<Narrow, W>, grid, dim3((W) * kWave), stream, tags, \
