@@ -190,8 +190,8 @@ def test_edge_shapes(pace, case, mask_frac, fused):
 @pytest.mark.parametrize("n", [8192, 8193])
 @FUSED
 def test_pool_at_rank_limit(pace, n, fused):
-    """8192 trajectories take the rank-and-piece kernels in the fused call,
-    8193 the separate ones."""
+    """8192 trajectories take the rank and the range copy in the fused call,
+    8193 the selection spread over the chip and the merge-path copy."""
     lens = np.random.default_rng(n).integers(0, 700, size=n)
     pool = poolgen.make_custom_pool(lens, V=80, seed=n, mask_frac=0.1, W=512)
     say("n=%d fused %s" % (n, fused))
@@ -200,7 +200,7 @@ def test_pool_at_rank_limit(pace, n, fused):
 
 @FUSED
 def test_pool_above_register_capacity(pace, fused):
-    """20000 trajectories: the fused call falls back to the separate kernels."""
+    """20000 trajectories, more than one workgroup's registers hold keys of."""
     lens = np.random.default_rng(9).integers(0, 400, size=20000)
     pool = poolgen.make_custom_pool(lens, V=60, seed=99, mask_frac=0.1, W=512)
     say("n=20000 fused %s" % fused)
@@ -217,7 +217,8 @@ def test_all_masked_trajectories(pace, fused):
     assert_same(gpu_step(pace, pool, fused=fused), r, "all-masked")
 
 
-def test_unaligned_tags_take_the_scalar_path(pace):
+def test_unaligned_tags(pace):
+    """Scores by trajectory and the range copy, from a column off 16-byte alignment."""
     pool = poolgen.make_pool("math", n=300)
     say("unaligned tags")
     big = torch.empty(pool.n_tokens + 1, dtype=torch.int32, device=DEV)
@@ -237,36 +238,36 @@ def test_unaligned_tags_take_the_scalar_path(pace):
 
 
 @FUSED
-def test_large_versions_take_the_wide_path(pace, fused):
+def test_large_versions_in_few_trajectories(pace, fused):
+    """64-bit sums of the scores by trajectory, one of them in many batches."""
     lens = [700, 20000, 5, 9000]
     pool = poolgen.make_custom_pool(lens, V=2 ** 30, seed=12, mask_frac=0.1, W=64)
-    say("wide versions V=2^30 fused %s" % fused)
+    say("large versions V=2^30 fused %s" % fused)
     assert_same(gpu_step(pace, pool, fused=fused), oracle_step(pool), "wide")
 
 
 @FUSED
 @pytest.mark.parametrize("V", [32766, 32767, 2 ** 24 - 2, 2 ** 24 - 1])
-def test_reduce_mode_limits(pace, V, fused):
-    """Every tag at V, next to the limits where the reduction changes its
-    arithmetic (packed 2^15, 32-bit 2^24): full windows of the largest tags
-    must neither carry into the packed count nor overflow a 32-bit window
-    sum. Lengths put offsets at window edges and many windows inside one
-    trajectory; a tenth of the tokens are masked."""
+def test_large_tags_by_trajectory(pace, V, fused):
+    """Every tag at V, around 2^15 and 2^24, in pools scored by trajectory: a
+    tenth of the tokens masked, lengths around multiples of 256 and one of many
+    batches. (The chunked reduction's limits at these versions are in
+    test_gpu_score_reduce.py.)"""
     lens = [70000, 1, 255, 256, 257, 3000, 0, 4096, 12345, 2047, 2049] + [300] * 40
     pool = poolgen.make_custom_pool(lens, V=V, seed=V % 1000, mask_frac=0.1, c_lag=0, W=64)
     pool.tags[:] = np.where(pool.tags == -1, -1, V).astype(np.int32)
     pool.completion[:] = V
-    say("reduce limits V=%d fused %s" % (V, fused))
+    say("large tags V=%d fused %s" % (V, fused))
     assert_same(gpu_step(pace, pool, fused=fused), oracle_step(pool), "V=%d" % V)
 
 
 @FUSED
-def test_large_versions_many_boundaries(pace, fused):
-    """64-bit window prefixes: short trajectories put boundaries in most
-    blocks of the reduction while tag + 1 reaches 2^30."""
+def test_large_versions_short_trajectories(pace, fused):
+    """64-bit sums in one wave per trajectory, most of them shorter than its
+    first loads, while tag + 1 reaches 2^30."""
     lens = np.random.default_rng(31).integers(0, 300, size=3000)
     pool = poolgen.make_custom_pool(lens, V=2 ** 30, seed=31, mask_frac=0.2, W=64)
-    say("wide versions, short trajectories fused %s" % fused)
+    say("large versions, short trajectories fused %s" % fused)
     assert_same(gpu_step(pace, pool, fused=fused), oracle_step(pool), "wide short")
 
 
@@ -283,8 +284,8 @@ def test_gamma_and_window_min(pace, gamma, fused):
 
 
 @FUSED
-def test_large_window_in_global_memory(pace, fused):
-    """A 6000-entry prefix window (beyond the LDS-staged size), gamma = 1."""
+def test_large_window(pace, fused):
+    """A 6000-entry prefix window, searched by each trajectory's workgroup, gamma = 1."""
     pool = poolgen.make_custom_pool(np.full(300, 100), V=50, seed=21, W=6000)
     params = pace.default_params(gamma=1)
     say("window 6000 fused %s" % fused)
