@@ -140,9 +140,8 @@ def test_wide_select_beyond_limit(pace):
 
 @FUSED
 def test_wide_multi_column_payload(pace, fused):
-    """Blocks of 64 with every column width: int32 and fp32 columns copy by
-    16-byte slots, the uint8 and int16 ones element by element, fp64 and
-    int64 by slots of two elements."""
+    """Blocks of 64 with every column width, each copied by 16-byte vectors at
+    whatever byte a span starts on."""
     pool = poolgen.make_pool("wide", n=20000, seed=9)
     rng = np.random.default_rng(9)
     N = pool.n_tokens
@@ -154,7 +153,8 @@ def test_wide_multi_column_payload(pace, fused):
 
 
 def test_wide_unaligned_columns(pace):
-    """Column pointers off 16-byte alignment take the element slots."""
+    """Column pointers off 16-byte alignment: the vectors are aligned in the
+    output, which starts elsewhere than the input."""
     pool = poolgen.make_pool("wide", n=12000, seed=13)
     r = oracle_step(pool)
     N = pool.n_tokens
