@@ -65,14 +65,27 @@ def parse():
 
 
 # (timer phase, kernel) of the fused step's launches: pools of up to 8192
-# trajectories (rank path), the tiny pool (ranked and compacted by one kernel),
-# and larger ones (level-0 histogram of the cut
+# trajectories (rank path), small ones (ranked and compacted by one kernel),
+# and larger ones of short trajectories (level-0 histogram of the cut
 # search, cut-and-classify, merge-path compaction over blocks of 64
 # trajectories)
-PHASES = ((0, "score_traj"), (2, "rank"), (3, "compact_piece"))
-PHASES_SMALL = ((0, "score_traj"), (3, "compact_piece"))
+PHASES = ((0, "score_traj"), (2, "rank"), (3, "compact_range"))
+PHASES_SMALL = ((0, "score_traj"), (3, "rank_compact_small"))
 PHASES_WIDE = ((0, "score_reduce"), (1, "score_finalize"), (2, "cut_hist"), (6, "classify"),
                (3, "compact_wide"))
+
+
+def small_step(n, n_tokens, n_cols, budget):
+    """Whether the library ranks and compacts in one kernel: small_step_ok of
+    csrc/rules.hpp."""
+    most = (1 << 19) * (2 if n <= 128 else 1) // max(n_cols, 1)
+    return n <= 256 and (int(n_tokens * ((n - budget) / n)) if n else 0) <= most
+
+
+def step_phases(n, n_tokens, n_cols, budget):
+    if n > 8192:
+        return PHASES_WIDE
+    return PHASES_SMALL if small_step(n, n_tokens, n_cols, budget) else PHASES
 
 
 def cpu_model():
@@ -116,11 +129,13 @@ def kernel_bytes(pool, n_keep_tok, col_bytes, W, use_prefix, cus):
                    written per trajectory, the histogram read, the block
                    partials (16 B per 64 trajectories) and their group sums
                    (16 B per 1024 trajectories) written;
-    compact_piece  every kept element of each column read and written, keep
+    compact_range  every kept element of each column read and written, keep
     compact_wide   flags and offsets (17 B per trajectory), the block
                    partials (and, for compact_wide, their group sums) read,
                    packed offsets (8 B) and kept ids (4 B) per kept
-                   trajectory and rejected ids (4 B per rejection) written."""
+                   trajectory and rejected ids (4 B per rejection) written;
+    rank_compact_small  the same without partials: score 8 B read and keep flag
+                   written instead."""
     n, N = pool.n, pool.n_tokens
     chunks = reduce_chunks(N, cus)
     wide = n > 8192
@@ -131,6 +146,7 @@ def kernel_bytes(pool, n_keep_tok, col_bytes, W, use_prefix, cus):
     budget = max(0, pool.occupancy - pool.capacity)
     kept = n - min(budget, n)
     pre = (8 * n + 8 * W) if use_prefix else 0
+    copied = sum(2 * e * n_keep_tok for e in col_bytes) + 12 * kept + 8 + 4 * budget
     return {
         "score_traj": 4 * N + 8 * (n + 1) + 4 * n + pre + 32 * n,
         "score_reduce": 4 * N + 8 * (n + 1) + 16 * n + 16 * chunks,
@@ -138,9 +154,8 @@ def kernel_bytes(pool, n_keep_tok, col_bytes, W, use_prefix, cus):
         "rank": 8 * n + 16 * n + n + 16 * blocks,
         "cut_hist": 8 * n + 2 * n + 16 * groups + 8192,
         "classify": 8 * n + 16 * n + 2 * n + n + 8192 + 16 * blocks + 16 * bgroups,
-        "compact_wide" if wide else "compact_piece":
-            sum(2 * e * n_keep_tok for e in col_bytes) + 17 * n + 16 * blocks
-            + (16 * bgroups if wide else 0) + 12 * kept + 8 + 4 * budget,
+        "compact_wide" if wide else "compact_range": copied + 17 * n + 16 * blocks + (16 * bgroups if wide else 0),
+        "rank_compact_small": copied + 25 * n,
     }
 
 
@@ -168,7 +183,7 @@ def score_traffic(kernel, config, cols):
     if rec is None or rec["kernel"] != kernel:
         return None
     h = hashlib.sha256()
-    for f in (kernel_source(kernel), "score_math.hpp", "device_util.hpp"):
+    for f in (kernel_source(kernel), "score_math.hpp", "device_util.hpp", "rules.hpp"):
         with open(os.path.join(ROOT, "paper_2609_36830_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return rec["bytes"] if rec["sha256"] == h.hexdigest() else None
@@ -270,7 +285,7 @@ def measure_pool(pace, pool, host_cols, mode, K, dev, stream, cus, config_name):
     ms = ev[0].elapsed_time(ev[1]) / K
     assert int(rot.nkt.item()) == n_keep_tok
     # each kernel timed by its own events, same rotation
-    phases = PHASES_SMALL if pool.n <= 64 else PHASES if pool.n <= 8192 else PHASES_WIDE
+    phases = step_phases(pool.n, pool.n_tokens, len(host_cols), budget)
     kev = [[(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in phases]
            for _ in range(K)]
     for pairs in kev:
