@@ -399,8 +399,7 @@ struct BlockSums {
 // columns, 15.2 us, now 10.4);
 // 60 to 64 VGPRs, so that eight workgroups share a CU and one's look-up hides
 // under the others' copies. All waves copy a long span part together; parts of
-// at most kWaveCopy bytes go to the waves in turn. offsets_out, kept_ids and
-// n_kept_tokens may be null (rejected ids only).
+// at most kWaveCopy bytes go to the waves in turn.
 // Against whole spans cut into pieces of 16,384 tokens with all columns in one
 // workgroup, a fused step: 10M kept tokens in 3 columns 86 -> 67 us, 16.9M in 4
 // columns 149 -> 97 us, 16.7M in one column 79 -> 71 us.
@@ -436,7 +435,7 @@ __global__ __launch_bounds__(kPT) void compact_range_kernel(
         if (kC > 0) __syncthreads();
         L.finish();
         C.finish();
-        if (q == 0 && threadIdx.x == 0 && offsets_out) {
+        if (q == 0 && threadIdx.x == 0) {
             offsets_out[C.all] = L.all;
             *n_kept_tokens = L.all;
         }
@@ -444,10 +443,8 @@ __global__ __launch_bounds__(kPT) void compact_range_kernel(
         const int64_t rank = C.before(b) + (int64_t)__popcll(ballot(kept) & lanes_below());
         const int64_t dst = L.before(b) + (wave_incl_scan_i64(len) - len);
         if (kept) {
-            if (offsets_out) {
-                offsets_out[rank] = dst;
-                kept_ids[rank] = (int32_t)i;
-            }
+            offsets_out[rank] = dst;
+            kept_ids[rank] = (int32_t)i;
         } else if (in && reject_ids) {
             const int64_t rr = i - rank;       // trajectories before i that were rejected
             if (rr < budget) reject_ids[rr] = (int32_t)i;
@@ -723,8 +720,7 @@ __global__ __launch_bounds__(kWideBlock * kGroupBlocks) void compact_partials_wi
 }
 
 // nb blocks in ng = ceil(nb / kGroupBlocks) <= kWideMaxGroups groups;
-// 4 * grid >= nb. offsets_out, kept_ids and n_kept_tokens may be null
-// (rejected ids only).
+// 4 * grid >= nb.
 __global__ __launch_bounds__(kPT) void compact_wide_kernel(
     const int64_t *__restrict__ off, int64_t n, int64_t NT, const uint8_t *__restrict__ keep,
     PieceParts parts, int64_t nb, CompactCols cols, int n_cols, int64_t *__restrict__ offsets_out,
@@ -873,7 +869,7 @@ __global__ __launch_bounds__(kPT) void compact_wide_kernel(
 
     // 3. Index outputs of block ib (after the copy: their stores would hold
     //    up the copy's first loads, one counter covering both).
-    if (q == 0 && t == 0 && offsets_out) {
+    if (q == 0 && t == 0) {
         offsets_out[s_gc[kWideMaxGroups]] = tot_l;
         *n_kept_tokens = tot_l;
     }
@@ -887,10 +883,8 @@ __global__ __launch_bounds__(kPT) void compact_wide_kernel(
         const int64_t rank = cb + (int64_t)__popcll(ballot(kept) & lanes_below());
         const int64_t dst = lb + (wave_incl_scan_i64(len) - len);
         if (kept) {
-            if (offsets_out) {
-                offsets_out[rank] = dst;
-                kept_ids[rank] = (int32_t)i;
-            }
+            offsets_out[rank] = dst;
+            kept_ids[rank] = (int32_t)i;
         } else if (i < n && reject_ids) {
             const int64_t rr = i - rank;           // trajectories before i that were rejected
             if (rr < budget) reject_ids[rr] = (int32_t)i;
@@ -1065,13 +1059,13 @@ hipError_t launch_compact_pieces(const int64_t *offsets, int64_t n, int64_t n_to
                                  const PieceParts &parts, const CompactCols &cols, int n_cols,
                                  int64_t *offsets_out, int32_t *kept_ids, int64_t *n_kept_tokens,
                                  int32_t *reject_ids, int64_t budget, int64_t max_kept,
-                                 hipStream_t stream, int blk, bool copy) {
+                                 hipStream_t stream, int blk) {
     const int64_t nb = (n + blk - 1) / blk;
     if (blk == kPieceBlock) {
         if (nb > 8 * kWave) return hipErrorInvalidValue;
         const int64_t n_idx = nb > 0 ? (nb + kPW - 1) / kPW : 1;
-        const int64_t n_rng = copy && n_cols > 0 ? range_count(n, n_tokens, n_cols, max_kept) : 0;
-        const dim3 grid((unsigned)(n_idx + n_rng), (unsigned)(copy && n_cols > 0 ? n_cols : 1));
+        const int64_t n_rng = n_cols > 0 ? range_count(n, n_tokens, n_cols, max_kept) : 0;
+        const dim3 grid((unsigned)(n_idx + n_rng), (unsigned)(n_cols > 0 ? n_cols : 1));
 #define PACE_RANGES(P)                                                                                          \
     return launch(kPhaseCompact, compact_range_kernel<P>, grid, dim3(kPT), stream, offsets, n, n_tokens, keep,  \
                   parts, nb, n_idx, n_rng, range_least(n, n_tokens), cols, offsets_out, kept_ids, n_kept_tokens, \
@@ -1083,12 +1077,12 @@ hipError_t launch_compact_pieces(const int64_t *offsets, int64_t n, int64_t n_to
     }
     if (blk != kWideBlock || (nb + kGroupBlocks - 1) / kGroupBlocks > kWideMaxGroups) return hipErrorInvalidValue;
     // Every workgroup indexes up to four blocks and copies an even share of
-    // the output: one resident round (four per CU) when copying.
+    // the output: one resident round (four per CU).
     int64_t wgs = (nb + kPW - 1) / kPW;
-    if (copy && wgs < resident_waves() / 16 * 4) wgs = resident_waves() / 16 * 4;
+    if (wgs < resident_waves() / 16 * 4) wgs = resident_waves() / 16 * 4;
     if (wgs < 1) wgs = 1;
     return launch(kPhaseCompact, compact_wide_kernel, dim3((unsigned)wgs), dim3(kPT), stream, offsets, n, n_tokens,
-                  keep, parts, nb, cols, copy ? n_cols : 0, offsets_out, kept_ids, n_kept_tokens, reject_ids, budget);
+                  keep, parts, nb, cols, n_cols, offsets_out, kept_ids, n_kept_tokens, reject_ids, budget);
 }
 
 hipError_t launch_compact_copy(const CompactCols &cols, int n_cols, int64_t n_tokens,
@@ -1112,7 +1106,7 @@ hipError_t launch_compact(const int64_t *offsets, int64_t n, int64_t n_tokens, c
         hipError_t e = launch_compact_partials(offsets, n, n_tokens, keep, w.parts, stream, blk);
         if (e != hipSuccess) return e;
         return launch_compact_pieces(offsets, n, n_tokens, keep, w.parts, cols, n_cols, offsets_out,
-                                     kept_ids, n_kept_tokens, nullptr, 0, n, stream, blk, true);
+                                     kept_ids, n_kept_tokens, nullptr, 0, n, stream, blk);
     }
     compact_scan_kernel<<<1, kT, 0, stream>>>(offsets, n, n_tokens, keep, offsets_out, kept_ids,
                                              n_kept_tokens, w.kept_src, w.chunk_first,

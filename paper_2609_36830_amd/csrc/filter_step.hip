@@ -77,8 +77,7 @@ hipError_t launch_filter_step(const int32_t *tags, const int64_t *offsets, int64
         if (e != hipSuccess) return e;
         const int64_t n_kept = n - (budget < n ? budget : n);
         return launch_compact_pieces(offsets, n, n_tokens, keep, cw.parts, cols, n_cols, offsets_out,
-                                     kept_ids, n_kept_tokens, reject_ids, budget, n_kept, stream, kWideBlock,
-                                     true);
+                                     kept_ids, n_kept_tokens, reject_ids, budget, n_kept, stream, kWideBlock);
     }
     if (rank_path && small_step_ok(n, n_tokens, n_cols, budget))
         return launch_rank_compact_small(score, offsets, n, n_tokens, budget, keep, cols, n_cols, offsets_out, kept_ids,

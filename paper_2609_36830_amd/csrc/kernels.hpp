@@ -246,12 +246,11 @@ hipError_t launch_compact_partials(const int64_t *offsets, int64_t n, int64_t n_
                                    const uint8_t *keep, const PieceParts &parts, hipStream_t stream,
                                    int blk = kPieceBlock);
 // blk: trajectories per block of the partials (kPieceBlock or kWideBlock).
-// copy = false launches the block workgroups only (rejected ids; no columns).
 hipError_t launch_compact_pieces(const int64_t *offsets, int64_t n, int64_t n_tokens, const uint8_t *keep,
                                  const PieceParts &parts, const CompactCols &cols, int n_cols,
                                  int64_t *offsets_out, int32_t *kept_ids, int64_t *n_kept_tokens,
                                  int32_t *reject_ids, int64_t budget, int64_t max_kept,
-                                 hipStream_t stream, int blk = kPieceBlock, bool copy = true);
+                                 hipStream_t stream, int blk = kPieceBlock);
 // Selection and compaction of the filter step in one launch, where
 // small_step_ok (scores as launch_rank takes them; n = 0 included).
 hipError_t launch_rank_compact_small(const double *score, const int64_t *offsets, int64_t n, int64_t n_tokens,
