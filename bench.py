@@ -195,10 +195,10 @@ def kernel_source(kernel):
 
 # config -> the score kernel, the digest of its sources and its HBM bytes per launch
 SCORE_COUNTERS = {
-    # profiles/filter_step_hbm_counters.md: FETCH_SIZE 99050.4 KiB, WRITE_SIZE 525.4 KiB
-    "stress": {"kernel": "score_traj", "sha256": "789ae5d69b5a52c03ba2135215363a79375a4d6d2ae7d70541264fb32f592c18", "bytes": 203393228},
-    # profiles/filter_step_hbm_counters.md: FETCH_SIZE 103743.5 KiB, WRITE_SIZE 1140.4 KiB
-    "wide": {"kernel": "score_reduce", "sha256": "d60133e0ff808e8d698bc292ce271a5cae10580bb69fcd1460566173d77fa5a4", "bytes": 213634457},
+    # profiles/filter_step_hbm_counters.md: FETCH_SIZE 99059.8 KiB, WRITE_SIZE 534.5 KiB
+    "stress": {"kernel": "score_traj", "sha256": "7ae3ba9c910e7ad39ff463c9aea06b5313d3ed513021cdea33d4fbce9cbb06dd", "bytes": 203421798},
+    # profiles/filter_step_hbm_counters.md: FETCH_SIZE 103748.4 KiB, WRITE_SIZE 1140.3 KiB
+    "wide": {"kernel": "score_reduce", "sha256": "4fb81e651c9ed548058884cd75cc00c706c663a672cff99c1be16c00668ab29b", "bytes": 213644390},
 }
 
 

@@ -337,8 +337,8 @@ __device__ void find_cut(const double *__restrict__ score, int64_t n, int64_t bu
         cnt = sm.ncand < (uint32_t)kCandCap ? sm.ncand : (uint32_t)kCandCap;
         if (cnt <= (uint32_t)kRankMax) {
             // Few enough to rank at once: the bin's key range (two wave
-            // reductions and a barrier) is not needed. 1.5 us of the
-            // 65,536-trajectory step.
+            // reductions and a barrier) is not needed. 1.2 us of the
+            // 65,536-trajectory step (the kernel 11.7 -> 10.4).
             if (t < (int)cnt) sm.ck[t] = score_key(score[sm.ci[t]]);
             __syncthreads();
             rank_candidates(cnt);
