@@ -605,7 +605,7 @@ constexpr int64_t kBlockCost = 2048;
 constexpr int kSpanT = kPT;               // spans in one copy table: four blocks of one wave each
 constexpr int kSpanU = 8;                 // 16-byte loads in flight per thread in a span copy
 struct SpanTable {
-    int32_t start[kSpanT + 1];   // first slot of each span; [kSpanT] = slots in the table
+    int32_t start[kSpanT];       // first slot of each span
     int64_t dst[kSpanT];         // byte offset of each span's first slot
     int64_t src[kSpanT];         // byte offset of its source
 };
@@ -644,31 +644,32 @@ __device__ __forceinline__ void copy_spans_col(const CompactCols &cols, int col,
     } else {
         copy_under16(src + a0 + dl, dst + a0, (int)(b0 - a0));
     }
-    __syncthreads();                           // the previous table is no longer read
+    // (The sum's barriers also end the reading of the previous table.)
     uint32_t tot;
     const uint32_t ex = block_excl_sum_u32<kPW>((uint32_t)((v1 - v0) / 16), tot, wsum);
-    tb.start[t] = (int32_t)ex;
-    if (t == kPT - 1) tb.start[kSpanT] = (int32_t)tot;
-    tb.dst[t] = v0;
-    tb.src[t] = v0 + dl;
-    __syncthreads();
-    const int32_t total = tb.start[kSpanT];
-    for (int32_t g0 = t; g0 < total; g0 += kSpanU * kPT) {
-        uint4 x[kSpanU];
+    if (tot != 0) {                            // there are slots
+        tb.start[t] = (int32_t)ex;
+        tb.dst[t] = v0;
+        tb.src[t] = v0 + dl;
+        __syncthreads();
+        const int32_t total = (int32_t)tot;
+        for (int32_t g0 = t; g0 < total; g0 += kSpanU * kPT) {
+            uint4 x[kSpanU];
 #pragma unroll
-        for (int u = 0; u < kSpanU; ++u) {
-            const int32_t g = g0 + u * kPT;
-            if (g < total) {
-                const int j = span_find(tb, g);
-                x[u] = load_a1(src + tb.src[j] + (int64_t)(g - tb.start[j]) * 16);
+            for (int u = 0; u < kSpanU; ++u) {
+                const int32_t g = g0 + u * kPT;
+                if (g < total) {
+                    const int j = span_find(tb, g);
+                    x[u] = load_a1(src + tb.src[j] + (int64_t)(g - tb.start[j]) * 16);
+                }
             }
-        }
 #pragma unroll
-        for (int u = 0; u < kSpanU; ++u) {
-            const int32_t g = g0 + u * kPT;
-            if (g < total) {
-                const int j = span_find(tb, g);
-                store_nt(reinterpret_cast<uint4 *>(dst + tb.dst[j] + (int64_t)(g - tb.start[j]) * 16), x[u]);
+            for (int u = 0; u < kSpanU; ++u) {
+                const int32_t g = g0 + u * kPT;
+                if (g < total) {
+                    const int j = span_find(tb, g);
+                    store_nt(reinterpret_cast<uint4 *>(dst + tb.dst[j] + (int64_t)(g - tb.start[j]) * 16), x[u]);
+                }
             }
         }
     }
